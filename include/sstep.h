@@ -153,8 +153,8 @@ typedef struct {
                                Sec. 4 (a diagnostic: its Gram matrix is badly conditioned; the
                                bounds are then unused; not for batched contexts) */
     int32_t basis_steps;    /* 0 (default) = two basis steps per launch where the kernels allow it
-                               (constant 7-point operator, or batched stencil systems, when AP is
-                               not stored); 1 = one step per launch everywhere.  Both give the
+                               (constant 7-point operator, large 27-point grids, or batched
+                               stencil systems, when AP is not stored); 1 = one step per launch everywhere.  Both give the
                                same basis bit for bit */
     void *stream;           /* hipStream_t the caller's data is ordered on (NULL = default) */
 } sstep_options;
@@ -289,8 +289,9 @@ int32_t sstep_gram_mode(const sstep_ctx *ctx);
 
 /* Kernel launches that form the basis p_1 .. p_m of one outer iteration
  * (Sec. 2, Definition; m = s - 1 with SSTEP_GRAM_APPLY_OP, else s).  With
- * basis_steps = 0, for the constant 7-point operator with the Chebyshev basis
- * and AP not stored, and for batched stencil systems with the recurrence Gram
+ * basis_steps = 0, for the constant 7-point operator (any size) and the
+ * 27-point operator (327680 unknowns or more) with the Chebyshev basis and AP
+ * not stored, and for batched stencil systems with the recurrence Gram
  * kind, one launch forms two consecutive columns (p_{j+1} and p_{j+2} from
  * p_{j-1} and p_j, exactly as two single steps would), and *pairs (if pairs
  * is not NULL) receives how many launches do so; an odd m ends with a single

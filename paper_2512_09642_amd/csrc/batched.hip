@@ -265,7 +265,6 @@ __global__ __launch_bounds__(kBlock) void k_bbasis(const BGlob *__restrict__ gl,
 // constant operator, whose diagonal the FGS kernel applies), and writes them
 // to the pair's product slots from slot 2j + 1 (0 when FIRST), one partial
 // per band (BSys::mofs).
-constexpr uint32_t kMark = 0x40000000u;
 template <typename T, bool FACES, bool FIRST, int D, int NT, bool MOM>
 __global__ __launch_bounds__(NT) void k_bbasis_f2(const BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                   const BF2Tile *__restrict__ tiles, uint32_t nbl,

@@ -691,49 +691,33 @@ hipError_t basis_t(const IterArgs &a, int j, int step, hipStream_t st)
     }
 }
 
-// Two basis steps per launch (basis_f2.h) for the constant 7-point operator,
-// shapes measured fastest on MI355X at 224^3: FP64 56-point tile rows
-// (64-byte aligned stores), 3 planes of loads in flight; FP32 62-point rows,
-// 6 planes.  With the moments Gram kind the products' FP64 accumulators take
-// registers, and DM planes in flight (2 and 3) are the most that keep the
-// kernel within 64 registers without spilling.  Ranges of 28 planes give 2 blocks per CU in one wave there;
-// smaller grids take thinner ranges to keep some 512 blocks.
-constexpr int kF2Rows = 16;
+// Two basis steps per launch (basis_f2.h) for the constant 7- and 27-point
+// operators: planes of loads in flight.  224^3 FP64: 76.6 us per pair on
+// average with 2 planes, 80.1 with 4 (more registers, the same bytes); FP32 4
+// (25.1 us at 187 x 173 x 191, 25.4 with 6).
 template <typename T>
-struct F2Shape;
-template <>
-struct F2Shape<double> {
-    static constexpr int D = 3, TXI = 56, DM = 2;
-};
-template <>
-struct F2Shape<float> {
-    static constexpr int D = 6, TXI = 62, DM = 3;
-};
+constexpr int kF2Depth = sizeof(T) == 8 ? 2 : 4;
 
-template <typename T>
-F2Plan f2_plan(const Grid3 &g)
-{
-    constexpr int TXI = F2Shape<T>::TXI;
-    const int64_t tiles = ((g.nx + TXI - 1) / TXI) * ((g.ny + kF2Rows - 3) / (kF2Rows - 2));
-    int kz = 28;
-    if (tiles * ((g.nz + kz - 1) / kz) < 512)
-        kz = static_cast<int>(std::max<int64_t>(4, std::min<int64_t>(28, g.nz * tiles / 512)));
-    return plan_f2<kF2Rows, TXI>(g, kz, 0);
-}
+// Unknowns from which the 27-point operator takes two steps per launch: a
+// pair's march is a serial chain of planes, which a small grid does not fill
+// the chip for (per outer iteration at s = 16: 64^3 144 us with single steps
+// against 162 with pairs, 80^3 219 against 177, 230^3 2.1x faster in pairs).
+constexpr int64_t kF2BoxMin = 5 * (int64_t(1) << 16);
 
-template <typename T>
-bool f2_fits(const IterArgs &a)
-{
-    return f2_window_bytes(a.op.g, f2_plan<T>(a.op.g).kz, sizeof(T)) < (int64_t(1) << 31);
-}
+bool f2_box(const IterArgs &a) { return a.op.kind == kOpPoisson27; }
 
-// The two-step kernel serves the Chebyshev basis of the constant 7-point
-// operator when AP is not stored (recurrence and operator-applying Gram kinds).
+F2Plan f2_plan(const IterArgs &a) { return plan_f2(a.op.g, f2_box(a), a.fp32 ? 4 : 8); }
+
+// The two-step kernel serves the Chebyshev basis of the constant operators
+// when AP is not stored (moments, recurrence and operator-applying Gram
+// kinds).
 bool basis_pairs_apply(const IterArgs &a)
 {
-    if (a.op.kind != kOpPoisson || a.AP || a.monomial || a.one_step)
+    if ((a.op.kind != kOpPoisson && a.op.kind != kOpPoisson27) || a.AP || a.monomial || a.one_step)
         return false;
-    return a.fp32 ? f2_fits<float>(a) : f2_fits<double>(a);
+    if (a.op.kind == kOpPoisson27 && a.op.n < kF2BoxMin)
+        return false;
+    return f2_window_bytes(a.op.g, f2_plan(a).kz, a.fp32 ? 4 : 8) <= kF2MaxWindow;
 }
 
 // Columns p_1 .. p_m a basis forms: m = s - 1 when the Gram kernel applies the
@@ -741,34 +725,35 @@ bool basis_pairs_apply(const IterArgs &a)
 // only; the recurrence kind forms p_s).
 int basis_columns(const IterArgs &a) { return a.gram_op ? a.s - 1 : a.s; }
 
-template <typename T>
-hipError_t basis_pair(const IterArgs &a, int j, hipStream_t st)
+template <typename T, bool BOX, bool MOM>
+hipError_t basis_pair_v(const IterArgs &a, int j, hipStream_t st)
 {
-    constexpr int D = F2Shape<T>::D, TXI = F2Shape<T>::TXI, DM = F2Shape<T>::DM;
-    const F2Plan plan = f2_plan<T>(a.op.g);
+    constexpr int D = kF2Depth<T>;
+    const F2Plan plan = f2_plan(a);
     T *P = static_cast<T *>(a.P);
     const T *pprev = j > 0 ? P + (j - 1) * a.ld : nullptr;
     const T *pj = P + j * a.ld;
     T *q = P + (j + 1) * a.ld, *p2 = P + (j + 2) * a.ld;
-    const T minv = a.op.precond ? T(1) / T(6) : T(1);
+    const T minv = a.op.precond ? T(1) / T(BOX ? 26 : 6) : T(1);
     const T theta = static_cast<T>(a.theta), sigma = static_cast<T>(a.sigma);
-    const dim3 grid(plan.per * kNumXcd), block(kF2Lanes * kF2Rows);
-    double *mp = a.gram_mom ? a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride : nullptr;
-    if (a.gram_mom) {
-        if (j == 0)
-            hipLaunchKernelGGL((k_basis_f2<T, kF2Rows, true, DM, 8, TXI, true>), grid, block, 0, st, a.st, a.op.g,
-                               minv, pprev, pj, q, p2, theta, sigma, plan, mp, a.mstride);
-        else
-            hipLaunchKernelGGL((k_basis_f2<T, kF2Rows, false, DM, 8, TXI, true>), grid, block, 0, st, a.st, a.op.g,
-                               minv, pprev, pj, q, p2, theta, sigma, plan, mp, a.mstride);
-    } else if (j == 0) {
-        hipLaunchKernelGGL((k_basis_f2<T, kF2Rows, true, D, 8, TXI, false>), grid, block, 0, st, a.st, a.op.g, minv,
-                           pprev, pj, q, p2, theta, sigma, plan, mp, a.mstride);
-    } else {
-        hipLaunchKernelGGL((k_basis_f2<T, kF2Rows, false, D, 8, TXI, false>), grid, block, 0, st, a.st, a.op.g,
-                           minv, pprev, pj, q, p2, theta, sigma, plan, mp, a.mstride);
-    }
+    const dim3 grid(plan.per * kNumXcd), block(kF2Threads);
+    double *mp = MOM ? a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride : nullptr;
+    if (j == 0)
+        hipLaunchKernelGGL((k_basis_f2<T, BOX, true, D, MOM>), grid, block, 0, st, a.st, a.op.g, minv, pprev, pj, q,
+                           p2, theta, sigma, plan, mp, a.mstride);
+    else
+        hipLaunchKernelGGL((k_basis_f2<T, BOX, false, D, MOM>), grid, block, 0, st, a.st, a.op.g, minv, pprev, pj,
+                           q, p2, theta, sigma, plan, mp, a.mstride);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t basis_pair(const IterArgs &a, int j, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 8)  // the moments kind is FP64 only
+        if (a.gram_mom)
+            return f2_box(a) ? basis_pair_v<T, true, true>(a, j, st) : basis_pair_v<T, false, true>(a, j, st);
+    return f2_box(a) ? basis_pair_v<T, true, false>(a, j, st) : basis_pair_v<T, false, false>(a, j, st);
 }
 
 // Sliced ELL from CSR (OpEll, common.h): one thread per row slot of every
@@ -990,7 +975,7 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
     };
     int j = 0;
     if (basis_pairs_apply(a)) {
-        const int64_t nbl = a.fp32 ? f2_plan<float>(a.op.g).nbl : f2_plan<double>(a.op.g).nbl;
+        const int64_t nbl = f2_plan(a).nbl;
         for (; j + 2 <= m; j += 2)
             put(j, 2, nbl);
     }
