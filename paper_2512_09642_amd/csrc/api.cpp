@@ -432,22 +432,18 @@ void set_gram_kind(IterArgs &it, int kind, int precond, bool const_diag)
     it.rec_hscale = (it.gram_rec && precond && const_diag) ? (it.op.kind == kOpPoisson27 ? 26.0 : 6.0) : 1.0;
 }
 
-// Residual kernel schedule: at most 1024 row chunks (one partial each), or
-// for the constant Poisson operator with an even x-extent the 1024-thread
-// blocks of 2 x-points x 8 planes when they number at most 1024.
+// Residual kernel schedule: the marched kernel's blocks for large grids of a
+// constant operator, else at most 1024 row chunks (one partial each).
 void set_residual_schedule(IterArgs &it)
 {
     const OpDev &op = it.op;
     const int64_t n = op.n;
     it.nbr = int(std::min<int64_t>(1024, (n + kBlock - 1) / kBlock));
     it.rchunk = round_up((n + it.nbr - 1) / it.nbr, kBlock);
-    it.res_p2 = 0;
-    if (op.kind == kOpPoisson && op.g.nx % 2 == 0) {
-        const int64_t blocks = ((op.g.nxy / 2 + 1023) / 1024) * ((op.g.nz + 7) / 8);
-        if (blocks <= 1024) {
-            it.res_p2 = 1;
-            it.nbr = int(blocks);
-        }
+    it.res_m = 0;
+    if (const int blocks = residual_march_blocks(op)) {
+        it.res_m = 1;
+        it.nbr = blocks;
     }
 }
 

@@ -148,6 +148,15 @@ __device__ __forceinline__ float buf_load(float, __amdgpu_buffer_rsrc_t r, uint3
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
+// A value read once.
+__device__ __forceinline__ double buf_load_once(double, __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, kNonTemporal));
+}
+__device__ __forceinline__ float buf_load_once(float, __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kNonTemporal));
+}
 // FP64 results are stored non-temporally, FP32 ones through the caches: the
 // 248-byte FP32 row pieces end mid-line, and L2 merges such partial lines
 // only for cached stores (FP32 pair 47 us cached against 62 us

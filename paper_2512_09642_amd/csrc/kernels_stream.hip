@@ -3,8 +3,8 @@
 // All of them are bound by HBM bandwidth (well under one flop per byte).
 #include <algorithm>
 
-#include "basis_f2.h"
 #include "launch.h"
+#include "march.h"
 #include "opsel.h"
 #include "stop.h"
 
@@ -87,70 +87,6 @@ __global__ __launch_bounds__(kBlock) void k_residual(const DevState *__restrict_
             p0[c] = static_cast<TP>(scale * (p0_mode ? r : dinv * r));
     }
     block_sum_store(acc, rpart + lb);
-}
-
-// The residual for the constant Poisson operator in FP64 (nx even) in the
-// basis kernel's shape: two x-points and kP2Kz planes per thread, 1024-thread
-// blocks, +-z neighbours of x from registers, b read once (non-temporal).
-// One partial sum of r^2 per block, blocks numbered blockIdx.x + gridDim.x *
-// blockIdx.y (the launch keeps their number within the partial buffer).
-template <typename TP>
-__global__ __launch_bounds__(1024) void k_residual_p2(const DevState *__restrict__ st, Grid3 g, double minv,
-                                                      TP *__restrict__ p0, double *__restrict__ rpart, int p0_mode,
-                                                      int write_p0)
-{
-    constexpr int KZ = 8;
-    __shared__ double part[1024 / kWave];
-    if (st->done)
-        return;
-    const double *__restrict__ x = st->x;
-    const double *__restrict__ b = st->b;
-    const double scale = st->p0scale;
-    const uint32_t pl = (blockIdx.x * 1024 + threadIdx.x) * 2;  // in-plane index of the pair
-    double acc = 0.0;
-    if (pl < static_cast<uint32_t>(g.nxy)) {
-        const uint32_t j = fdiv(pl, g.dx);
-        const uint32_t i = pl - j * g.nx;
-        const int k0 = blockIdx.y * KZ;
-        const double2 z = {0.0, 0.0};
-        int64_t c = pl + static_cast<int64_t>(k0) * g.nxy;
-        double2 below = k0 > 0 ? *reinterpret_cast<const double2 *>(x + c - g.nxy) : z;
-        double2 ctr = *reinterpret_cast<const double2 *>(x + c);
-#pragma unroll
-        for (int kk = 0; kk < KZ; ++kk) {
-            const int k = k0 + kk;
-            if (k >= g.nz)
-                break;
-            const double2 above = k + 1 < g.nz ? *reinterpret_cast<const double2 *>(x + c + g.nxy) : z;
-            const double w = i > 0 ? x[c - 1] : 0.0;
-            const double e = i + 2 < static_cast<uint32_t>(g.nx) ? x[c + 2] : 0.0;
-            const double2 s = j > 0 ? *reinterpret_cast<const double2 *>(x + c - g.nx) : z;
-            const double2 nn = j + 1 < static_cast<uint32_t>(g.ny) ? *reinterpret_cast<const double2 *>(x + c + g.nx) : z;
-            const double bx = __builtin_nontemporal_load(b + c), by = __builtin_nontemporal_load(b + c + 1);
-            const double yx = 6.0 * ctr.x - (((((w + ctr.y) + s.x) + nn.x) + below.x) + above.x);
-            const double yy = 6.0 * ctr.y - (((((ctr.x + e) + s.y) + nn.y) + below.y) + above.y);
-            const double rx = bx - yx, ry = by - yy;
-            acc += rx * rx;
-            acc += ry * ry;
-            if (write_p0) {
-                p0[c] = static_cast<TP>(scale * (p0_mode ? rx : minv * rx));
-                p0[c + 1] = static_cast<TP>(scale * (p0_mode ? ry : minv * ry));
-            }
-            below = ctr;
-            ctr = above;
-            c += g.nxy;
-        }
-    }
-    acc = wave_sum(acc);
-    if (threadIdx.x % kWave == 0)
-        part[threadIdx.x / kWave] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double sum = 0.0;
-        for (int w = 0; w < 1024 / kWave; ++w)
-            sum += part[w];
-        rpart[blockIdx.x + gridDim.x * blockIdx.y] = sum;
-    }
 }
 
 // One step of the Chebyshev recurrence fused with the operator apply
@@ -560,19 +496,49 @@ hipError_t residual_for(const IterArgs &a, const Op &op, hipStream_t st, bool wr
     return hipGetLastError();
 }
 
+// Where a marched kernel (march.h) takes the place of one point per thread.
+// A march is a serial chain of planes in a few hundred blocks: small grids
+// are faster with a thread per point.  Residual with its stopping test at
+// 64^3 / 96^3 / 224^3: 27-point 9.3 / 23.6 / 288 us one point per thread
+// against 10.1 / 15.4 / 53 marched; 7-point 8.3 / 13.1 / 49.6 marched.
+constexpr int64_t kMarchResidual = 5 * (int64_t(1) << 16);
+// One basis step, by the bytes of a vector: 27-point FP64 64^3 / 96^3 / 224^3
+// 6.9 / 17.4 / 162 us against 8.6 / 12.4 / 52, FP32 96^3 / 128^3 8.0 / 16.9
+// against 8.6 / 11.2; 7-point FP64 with products 128^3 / 160^3 / 224^3 15.2 /
+// 25.9 / 67 against 15.9 / 23.1 / 47.5, FP32 the same at 160^3 and 224^3.
+constexpr int64_t kMarchStep27 = int64_t(4) << 20, kMarchStep7 = int64_t(24) << 20;
+
+bool march_fits(const OpDev &op, int elem)
+{
+    return (op.kind == kOpPoisson || op.kind == kOpPoisson27) &&
+           f2_window_bytes(op.g, plan_march(op.g, op.kind == kOpPoisson27, elem).kz, elem) <= kF2MaxWindow;
+}
+
+bool march_step(const OpDev &op, int elem)
+{
+    return op.n * elem >= (op.kind == kOpPoisson27 ? kMarchStep27 : kMarchStep7) && march_fits(op, elem);
+}
+
+template <typename TP, bool BOX>
+hipError_t residual_march(const IterArgs &a, hipStream_t st, bool write_p0)
+{
+    const F2Plan plan = plan_march(a.op.g, BOX, 8);
+    if (static_cast<int>(plan.nbl) != a.nbr)
+        return hipErrorInvalidValue;  // rpart holds nbr partials
+    hipLaunchKernelGGL((k_residual_m<TP, BOX>), dim3(plan.per * kNumXcd), dim3(kF2Threads), 0, st, a.st, a.op.g,
+                       a.op.precond ? 1.0 / (BOX ? 26.0 : 6.0) : 1.0, static_cast<TP *>(a.P), a.rpart, a.p0_mode,
+                       write_p0 ? 1 : 0, plan);
+    return hipGetLastError();
+}
+
 template <typename TP>
 hipError_t residual_t(const IterArgs &a, hipStream_t st, bool write_p0)
 {
+    if (a.res_m)
+        return a.op.kind == kOpPoisson27 ? residual_march<TP, true>(a, st, write_p0)
+                                         : residual_march<TP, false>(a, st, write_p0);
     switch (a.op.kind) {
     case kOpPoisson:
-        if (a.res_p2) {
-            const dim3 grid(static_cast<uint32_t>((a.op.g.nxy / 2 + 1023) / 1024),
-                            static_cast<uint32_t>((a.op.g.nz + 7) / 8));
-            hipLaunchKernelGGL(k_residual_p2<TP>, grid, dim3(1024), 0, st, a.st, a.op.g,
-                               a.op.precond ? 1.0 / 6.0 : 1.0, static_cast<TP *>(a.P), a.rpart, a.p0_mode,
-                               write_p0 ? 1 : 0);
-            return hipGetLastError();
-        }
         return residual_for<OpPoisson7<double>, TP>(a, make_poisson<double>(a.op), st, write_p0);
     case kOpFaces:
         return residual_for<OpFaces7<double>, TP>(a, Ops<double>::faces(a.op), st, write_p0);
@@ -583,6 +549,39 @@ hipError_t residual_t(const IterArgs &a, hipStream_t st, bool write_p0)
             return residual_for<OpEll<double>, TP>(a, Ops<double>::ell(a.op), st, write_p0);
         return residual_for<OpCsr<double>, TP>(a, Ops<double>::csr(a.op), st, write_p0);
     }
+}
+
+template <typename T, bool BOX>
+hipError_t basis_march(const IterArgs &a, int j, int step, hipStream_t st)
+{
+    const F2Plan plan = plan_march(a.op.g, BOX, sizeof(T));
+    T *P = static_cast<T *>(a.P);
+    T *AP = static_cast<T *>(a.AP);
+    const T *pj = P + j * a.ld;
+    const T *pprev = j > 0 ? P + (j - 1) * a.ld : nullptr;
+    T *apj = AP ? AP + j * a.ld : nullptr;
+    T *pnext = P + (j + 1) * a.ld;
+    const T minv = a.op.precond ? T(1) / T(BOX ? 26 : 6) : T(1);
+    const T theta = static_cast<T>(a.theta), sigma = static_cast<T>(a.sigma);
+    const dim3 grid(plan.per * kNumXcd), block(kF2Threads);
+    if constexpr (sizeof(T) == 8)  // the moments kind is FP64 only
+        if (a.gram_mom) {
+            double *mp = a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride;
+            if (step == 0)
+                hipLaunchKernelGGL((k_basis_m<T, BOX, 0, true>), grid, block, 0, st, a.st, a.op.g, minv, pj, pprev,
+                                   apj, pnext, theta, sigma, plan, mp, a.mstride);
+            else
+                hipLaunchKernelGGL((k_basis_m<T, BOX, 1, true>), grid, block, 0, st, a.st, a.op.g, minv, pj, pprev,
+                                   apj, pnext, theta, sigma, plan, mp, a.mstride);
+            return hipGetLastError();
+        }
+    if (step == 0)
+        hipLaunchKernelGGL((k_basis_m<T, BOX, 0, false>), grid, block, 0, st, a.st, a.op.g, minv, pj, pprev, apj,
+                           pnext, theta, sigma, plan, nullptr, a.mstride);
+    else
+        hipLaunchKernelGGL((k_basis_m<T, BOX, 1, false>), grid, block, 0, st, a.st, a.op.g, minv, pj, pprev, apj,
+                           pnext, theta, sigma, plan, nullptr, a.mstride);
+    return hipGetLastError();
 }
 
 template <class Op, typename T>
@@ -674,6 +673,8 @@ hipError_t basis_csr(const IterArgs &a, int j, int step, hipStream_t st)
 template <typename T>
 hipError_t basis_t(const IterArgs &a, int j, int step, hipStream_t st)
 {
+    if (step != 2 && march_step(a.op, sizeof(T)))
+        return a.op.kind == kOpPoisson27 ? basis_march<T, true>(a, j, step, st) : basis_march<T, false>(a, j, step, st);
     switch (a.op.kind) {
     case kOpPoisson:
         if constexpr (sizeof(T) == 8)
@@ -900,6 +901,13 @@ hipError_t launch_check_csr_cols(const int32_t *rp, const int32_t *ci, int64_t n
     return hipGetLastError();
 }
 
+int residual_march_blocks(const OpDev &op)
+{
+    return op.n >= kMarchResidual && march_fits(op, 8)
+               ? static_cast<int>(plan_march(op.g, op.kind == kOpPoisson27, 8).nbl)
+               : 0;
+}
+
 hipError_t launch_residual(const IterArgs &a, hipStream_t st, bool write_p0)
 {
     const hipError_t e = a.fp32 ? residual_t<float>(a, st, write_p0) : residual_t<double>(a, st, write_p0);
@@ -979,8 +987,12 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
         for (; j + 2 <= m; j += 2)
             put(j, 2, nbl);
     }
+    const int elem = a.fp32 ? 4 : 8;
+    const int64_t single = march_step(a.op, elem)
+                               ? plan_march(a.op.g, a.op.kind == kOpPoisson27, elem).nbl
+                               : plan_points(a.op.n).nbl;
     for (; j < m; ++j)
-        put(j, 1, plan_points(a.op.n).nbl);
+        put(j, 1, single);
     *stride = mx;
 }
 

@@ -66,7 +66,7 @@ struct IterArgs {
     double *rpart = nullptr;  // residual-norm partial sums [nbr]
     int nbr = 0;
     int64_t rchunk = 0;
-    int res_p2 = 0;  // constant Poisson, nx even: residual in the basis kernel's shape (nbr = its blocks)
+    int res_m = 0;   // constant operators: marched residual (march.h; nbr = its blocks)
     double *gpart = nullptr;  // Gram partial sums [E][nbg]
     double *gsum = nullptr;   // totals: the E Gram entries, then ||r||^2 (E + 1 doubles)
     int nbg = 0;
@@ -253,6 +253,9 @@ hipError_t launch_coarse_prepare(const CoarseArgs &c, hipStream_t st);
 hipError_t launch_coarse_fgs(const CoarseArgs &c, const double *f, double *u, int nu, hipStream_t st);
 
 hipError_t launch_residual(const IterArgs &a, hipStream_t st, bool write_p0);
+// Blocks (= partials) of the marched residual of a constant operator, 0 where
+// it does not serve the operator.
+int residual_march_blocks(const OpDev &op);
 hipError_t launch_p0scale(const IterArgs &a, hipStream_t st);
 hipError_t launch_basis(const IterArgs &a, int j, hipStream_t st);
 // Sliced ELL copy of a CSR operator: the columns (pattern) and the values in

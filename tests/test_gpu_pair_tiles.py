@@ -12,7 +12,8 @@ import pytest
 import torch
 
 import gen
-from helpers import rel
+import oracle
+from helpers import make_operator, oracle_rhs, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +47,32 @@ def test_pair_columns_equal_single_steps(hip, op, dims, precision):
     if got[0] is not None:
         assert torch.equal(got[0]["P"], got[1]["P"])
         assert rel(got[0]["G"], got[1]["G"]) <= (1e-10 if precision == "fp64" else 0.0)
+
+
+# grids that take the marched residual (327680 unknowns) and the marched single
+# step (27-point: 524288, 7-point: 3145728), at the edges of its 62 x 30 tiles
+MARCHED = [("7", (62, 30, 177)), ("7", (63, 31, 169)), ("7", (186, 181, 94)), ("27", (64, 65, 127)),
+           ("27", (61, 31, 280)), ("27", (125, 92, 46)), ("27", (380, 700, 2))]
+
+
+@pytest.mark.parametrize("op,dims", MARCHED)
+def test_marched_residual_and_step_lockstep(hip, op, dims):
+    """One step per launch (three columns) against the oracle at the lockstep
+    bars: residual norm and columns 1e-12, G, ctil, atil and x 1e-10."""
+    pr = (gen.small_poisson3d if op == "7" else gen.small_poisson27)(*dims, seed=sum(dims), s=3, nu=10)
+    A, b = oracle_rhs(pr)
+    bt = torch.as_tensor(b, device=DEV)
+    x = np.zeros(pr.n)
+    with hip.Solver(make_operator(hip, pr, "stencil"), 3, 10, pr.lmin, pr.lmax, basis_steps=1) as sv:
+        for k in range(2):
+            xt = torch.as_tensor(x, device=DEV)
+            g = sv.step(bt, xt, want_basis=True)
+            o = oracle.step(A, b, x, 3, 10, pr.lmin, pr.lmax, want_basis=True)
+            assert abs(g["rnorm"] - o["rnorm"]) <= 1e-12 * o["rnorm"]
+            P = g["P"].cpu().numpy()
+            for j in range(3):
+                assert rel(P[j], o["P"][j]) <= 1e-12, (k, j)
+            for key in ("G", "ctil", "atil"):
+                assert rel(g[key], o[key]) <= 1e-10, (k, key)
+            x = xt.cpu().numpy()
+            assert rel(x, o["x"]) <= 1e-10, k
