@@ -1940,8 +1940,10 @@ static sstep_status coarse_setup_impl(sstep_ctx *ctx, const sstep_operator *Af, 
         const int I = int(j % c.ncx), J = int((j / c.ncx) % c.ncy), K = int(j / (int64_t(c.ncx) * c.ncy));
         ++count[size_t(I + 2 * J + 4 * K) + 1];
     }
-    for (int t = 0; t < c.nwf; ++t)
+    for (int t = 0; t < c.nwf; ++t) {
         wf[size_t(t) + 1] = wf[size_t(t)] + count[size_t(t) + 1];
+        c.max_front = std::max(c.max_front, int(count[size_t(t) + 1]));
+    }
     std::vector<int32_t> fill(wf.begin(), wf.end() - 1);
     for (int64_t j = 0; j < nc; ++j) {
         const int I = int(j % c.ncx), J = int((j / c.ncx) % c.ncy), K = int(j / (int64_t(c.ncx) * c.ncy));

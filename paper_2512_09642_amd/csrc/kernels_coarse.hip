@@ -18,9 +18,20 @@
 // need dI + 2dJ + 4dK = 0 with |d| <= 1), and every neighbour with a lower
 // index has a lower t, so processing the wavefronts in order, the unknowns of
 // one wavefront in parallel, sees exactly the values of the sequential sweep.
-// One workgroup runs the sweeps (one wave per unknown, a barrier between
-// wavefronts); the whole solve is latency-bound (ν (ncx + 2ncy + 4ncz)
-// dependent steps), the data (v, u, f, coefficients) are L2-resident.
+// The sweeps overlap: a neighbour's t differs by at most 1 + 2 + 4 = 7, so
+// sweep l may process wavefront t at step t + 8 l: every neighbour of lower t
+// has then been updated in sweep l (at a step at least one earlier), every
+// neighbour of higher t in sweep l - 1 (at step t' + 8 (l - 1) <= t + 8 l - 1)
+// and none yet in the sweep after, and two unknowns of one step are never
+// neighbours (their t differ by a multiple of 8), so neither their values nor
+// the fine points of their supports meet.  nu sweeps take ncx + 2 ncy + 4 ncz -
+// 6 + 8 (nu - 1) dependent steps instead of nu times the wavefronts: 265
+// against 2260 at 17^3 and nu = 20.
+//
+// A step is one launch over all its unknowns, half a wave each, or, for small
+// hierarchies, one pass of a single block with a barrier behind it (the rule
+// is at launch_coarse_fgs).  The solve is bound by the chain of steps; its
+// data (v, u, f, coefficients) are L2-resident.
 #include <algorithm>
 
 #include "launch.h"
@@ -29,7 +40,8 @@ namespace sstep {
 namespace {
 
 constexpr int kCoarseThreads = 1024;
-constexpr int kCoarseWaves = kCoarseThreads / kWave;
+// What one block keeps in LDS: the wavefront starts and the unknowns in order.
+constexpr int kCoarseMaxFronts = 1023, kCoarseMaxUnknowns = 4096;
 
 // 1D hat of the trilinear basis: 1 at fine distance 0, 1/2 at 1, else 0.
 __device__ __forceinline__ double hat(int d) { return d == 0 ? 1.0 : (d == 1 || d == -1 ? 0.5 : 0.0); }
@@ -138,65 +150,153 @@ __global__ __launch_bounds__(kBlock) void k_coarse_zero(double *__restrict__ a, 
         a[q] = 0.0;
 }
 
-// The sweeps, streamed: lane l < 27 of the wave that updates unknown j owns
-// fine point (2I + l%3, 2J + (l/3)%3, 2K + l/9) of p_j's support.
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_fgs_streamed(
-    FineOp op, int ncx, int ncy, const double *__restrict__ diag, const double *__restrict__ f,
-    double *__restrict__ u, double *__restrict__ v, const int32_t *__restrict__ order,
-    const int32_t *__restrict__ wf, int nwf, int nu)
+constexpr int kHalf = kWave / 2;  // lanes per unknown
+
+// v plus the value of the lane that a DPP control selects.
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double v)
 {
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const Mem vm{v};
-    for (int sweep = 0; sweep < nu; ++sweep)
-        for (int t = 0; t < nwf; ++t) {
-            for (int q = wf[t] + wave; q < wf[t + 1]; q += kCoarseWaves) {
-                const int j = order[q];
-                int I, J, K;
-                coarse_ijk(j, ncx, ncy, I, J, K);
-                double w = 0.0, contrib = 0.0;
-                int64_t c = 0;
-                if (lane < 27) {
-                    const int dx = lane % 3, dy = (lane / 3) % 3, dz = lane / 9;
-                    const int x = 2 * I + dx, y = 2 * J + dy, z = 2 * K + dz;
-                    w = hat(dx - 1) * hat(dy - 1) * hat(dz - 1);
-                    c = x + op.nx * (static_cast<int64_t>(y) + static_cast<int64_t>(op.ny) * z);
-                    contrib = w * op.apply(vm, x, y, z);
-                }
-                const double ajv = wave_sum(contrib);  // (A_c u)_j = p_j^T A_f v
-                const double step = (f[j] - ajv) / diag[j];
-                if (lane == 0)
-                    u[j] += step;
-                if (lane < 27)
-                    v[c] += step * w;
-            }
-            __syncthreads();
-        }
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
 }
 
-// The sweeps with A_c formed: lane o < 27 holds entry o of row j.
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_fgs_formed(
-    int ncx, int ncy, int ncz, const double *__restrict__ rows, const double *__restrict__ f, double *__restrict__ u,
-    const int32_t *__restrict__ order, const int32_t *__restrict__ wf, int nwf, int nu)
+__device__ __forceinline__ double lane_value(double v, int l)
 {
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    for (int sweep = 0; sweep < nu; ++sweep)
-        for (int t = 0; t < nwf; ++t) {
-            for (int q = wf[t] + wave; q < wf[t + 1]; q += kCoarseWaves) {
-                const int j = order[q];
-                int I, J, K;
-                coarse_ijk(j, ncx, ncy, I, J, K);
-                double contrib = 0.0;
-                if (lane < 27 && lane != 13) {
-                    const int I2 = I + lane % 3 - 1, J2 = J + (lane / 3) % 3 - 1, K2 = K + lane / 9 - 1;
-                    if (I2 >= 0 && I2 < ncx && J2 >= 0 && J2 < ncy && K2 >= 0 && K2 < ncz)
-                        contrib = rows[static_cast<int64_t>(j) * 27 + lane] * u[I2 + ncx * (J2 + ncy * K2)];
-                }
-                const double off = wave_sum(contrib);
-                if (lane == 0)
-                    u[j] = (f[j] - off) / rows[static_cast<int64_t>(j) * 27 + 13];
-            }
-            __syncthreads();
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Sum over the 32 lanes of a half wave, in a fixed order; every lane gets it.
+// Within a row of 16 lanes by DPP (neighbours, pairs, the mirrored half row,
+// the mirrored row), then the two rows of the half.
+__device__ __forceinline__ double half_sum(double v)
+{
+    v = add_dpp<0xB1>(v);   // quad_perm 1,0,3,2
+    v = add_dpp<0x4E>(v);   // quad_perm 2,3,0,1
+    v = add_dpp<0x141>(v);  // row_half_mirror
+    v = add_dpp<0x140>(v);  // row_mirror
+    const double a = lane_value(v, 0) + lane_value(v, 16), b = lane_value(v, 32) + lane_value(v, 48);
+    return threadIdx.x % kWave < kHalf ? a : b;
+}
+
+// One update of unknown j by half a wave, streamed: lane l < 27 owns fine
+// point (2I + l%3, 2J + (l/3)%3, 2K + l/9) of p_j's support.
+struct Streamed {
+    static constexpr int64_t kBlockActive = 25;
+    FineOp op;
+    int ncx, ncy;
+    const double *diag, *f;
+    double *u, *v;
+
+    __device__ __forceinline__ void update(int j, int lane) const
+    {
+        int I, J, K;
+        coarse_ijk(j, ncx, ncy, I, J, K);
+        const double fj = f[j], dj = diag[j];
+        const int dx = lane % 3, dy = (lane / 3) % 3, dz = lane / 9;
+        const int x = 2 * I + dx, y = 2 * J + dy, z = 2 * K + dz;
+        const int64_t c = x + op.nx * (static_cast<int64_t>(y) + static_cast<int64_t>(op.ny) * z);
+        double w = 0.0, contrib = 0.0;
+        if (lane < 27) {
+            w = hat(dx - 1) * hat(dy - 1) * hat(dz - 1);
+            contrib = w * op.apply(Mem{v}, x, y, z);
         }
+        const double ajv = half_sum(contrib);  // (A_c u)_j = p_j^T A_f v
+        const double step = (fj - ajv) / dj;
+        if (lane == 0)
+            u[j] += step;
+        if (lane < 27)
+            v[c] += step * w;
+    }
+};
+
+// The same with A_c formed: lane o < 27 holds entry o of row j.
+struct Formed {
+    static constexpr int64_t kBlockActive = 56;
+    int ncx, ncy, ncz;
+    const double *rows, *f;
+    double *u;
+
+    __device__ __forceinline__ void update(int j, int lane) const
+    {
+        int I, J, K;
+        coarse_ijk(j, ncx, ncy, I, J, K);
+        const double fj = f[j], dj = rows[static_cast<int64_t>(j) * 27 + 13];
+        double contrib = 0.0;
+        if (lane < 27 && lane != 13) {
+            const int I2 = I + lane % 3 - 1, J2 = J + (lane / 3) % 3 - 1, K2 = K + lane / 9 - 1;
+            if (I2 >= 0 && I2 < ncx && J2 >= 0 && J2 < ncy && K2 >= 0 && K2 < ncz)
+                contrib = rows[static_cast<int64_t>(j) * 27 + lane] * u[I2 + ncx * (J2 + ncy * K2)];
+        }
+        const double off = half_sum(contrib);
+        if (lane == 0)
+            u[j] = (fj - off) / dj;
+    }
+};
+
+// One step: block row y takes sweep first + y, i.e. wavefront t0 - 8 y.
+template <class Form>
+__global__ __launch_bounds__(kBlock) void k_coarse_step(Form form, const int32_t *__restrict__ order,
+                                                        const int32_t *__restrict__ wf, int t0)
+{
+    const int t = t0 - 8 * static_cast<int>(blockIdx.y);
+    const int q = wf[t] + (static_cast<int>(blockIdx.x) * kBlock + static_cast<int>(threadIdx.x)) / kHalf;
+    if (q < wf[t + 1])  // the same for a half wave
+        form.update(order[q], threadIdx.x % kHalf);
+}
+
+// All steps in one block, a barrier behind each.
+template <class Form>
+__global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(Form form, const int32_t *__restrict__ order,
+                                                                  const int32_t *__restrict__ wf, int nwf, int nu)
+{
+    __shared__ int32_t start[kCoarseMaxFronts + 1], unknown[kCoarseMaxUnknowns];
+    for (int t = threadIdx.x; t <= nwf; t += kCoarseThreads)
+        start[t] = wf[t];
+    for (int q = threadIdx.x; q < wf[nwf]; q += kCoarseThreads)
+        unknown[q] = order[q];
+    __syncthreads();
+    const int half = threadIdx.x / kHalf, lane = threadIdx.x % kHalf;
+    for (int64_t step = 0; step < nwf + int64_t(8) * (nu - 1); ++step) {
+        const int64_t l0 = step < nwf ? 0 : (step - nwf) / 8 + 1, l1 = step / 8 < nu - 1 ? step / 8 : nu - 1;
+        int skip = half;  // unknowns of this step before the half wave's next one
+        for (int64_t l = l0; l <= l1; ++l) {
+            const int t = static_cast<int>(step - 8 * l), n = start[t + 1] - start[t];
+            for (; skip < n; skip += kCoarseThreads / kHalf)
+                form.update(unknown[start[t] + skip], lane);
+            skip -= n;
+        }
+        __syncthreads();
+    }
+}
+
+// One block while it has few unknowns per step (kBlockActive of the form, on
+// average): a launch costs some 2 us whatever it holds, a pass of the block
+// grows with the unknowns its 32 half waves take in turn.  nu = 20, one block /
+// launches / the sweeps one after another in one block, us: streamed 5^3 471 /
+// 581 / 863, 7^3 770 / 666 / 1636, 17^3 8400 / 1200 / 16137; formed 7^3 380 /
+// 492 / 942, 9^3 624 / 533 / 1551, 17^3 3300 / 790 / 6966; 31^3 streamed 1.95
+// against 95 ms.
+template <class Form>
+hipError_t run_sweeps(const CoarseArgs &c, const Form &form, int nu, hipStream_t st)
+{
+    if (nu < 1)
+        return hipGetLastError();
+    const int64_t nc = static_cast<int64_t>(c.ncx) * c.ncy * c.ncz;
+    const int64_t steps = c.nwf + int64_t(8) * (nu - 1);
+    if (c.nwf <= kCoarseMaxFronts && nc <= kCoarseMaxUnknowns && nc * nu <= Form::kBlockActive * steps) {
+        hipLaunchKernelGGL((k_coarse_sweeps<Form>), dim3(1), dim3(kCoarseThreads), 0, st, form, c.order, c.wf, c.nwf,
+                           nu);
+        return hipGetLastError();
+    }
+    const uint32_t bx = static_cast<uint32_t>((c.max_front * kHalf + kBlock - 1) / kBlock);
+    for (int64_t step = 0; step < steps; ++step) {
+        const int64_t l0 = step < c.nwf ? 0 : (step - c.nwf) / 8 + 1, l1 = std::min<int64_t>(step / 8, nu - 1);
+        hipLaunchKernelGGL((k_coarse_step<Form>), dim3(bx, static_cast<uint32_t>(l1 - l0 + 1)), dim3(kBlock), 0, st,
+                           form, c.order, c.wf, static_cast<int>(step - 8 * l0));
+    }
+    return hipGetLastError();
 }
 
 FineOp fine_op(const CoarseArgs &c)
@@ -224,17 +324,12 @@ hipError_t launch_coarse_fgs(const CoarseArgs &c, const double *f, double *u, in
     const int64_t nc = static_cast<int64_t>(c.ncx) * c.ncy * c.ncz;
     hipLaunchKernelGGL(k_coarse_zero, dim3(static_cast<uint32_t>(std::min<int64_t>((nc + kBlock - 1) / kBlock, 1024))),
                        dim3(kBlock), 0, st, u, nc);
-    if (c.rows) {
-        hipLaunchKernelGGL(k_coarse_fgs_formed, dim3(1), dim3(kCoarseThreads), 0, st, c.ncx, c.ncy, c.ncz, c.rows, f,
-                           u, c.order, c.wf, c.nwf, nu);
-    } else {
-        const int64_t nf = static_cast<int64_t>(c.nfx) * c.nfy * c.nfz;
-        hipLaunchKernelGGL(k_coarse_zero, dim3(static_cast<uint32_t>(std::min<int64_t>((nf + kBlock - 1) / kBlock, 1024))),
-                           dim3(kBlock), 0, st, c.v, nf);
-        hipLaunchKernelGGL(k_coarse_fgs_streamed, dim3(1), dim3(kCoarseThreads), 0, st, fine_op(c), c.ncx, c.ncy,
-                           c.diag, f, u, c.v, c.order, c.wf, c.nwf, nu);
-    }
-    return hipGetLastError();
+    if (c.rows)
+        return run_sweeps(c, Formed{c.ncx, c.ncy, c.ncz, c.rows, f, u}, nu, st);
+    const int64_t nf = static_cast<int64_t>(c.nfx) * c.nfy * c.nfz;
+    hipLaunchKernelGGL(k_coarse_zero, dim3(static_cast<uint32_t>(std::min<int64_t>((nf + kBlock - 1) / kBlock, 1024))),
+                       dim3(kBlock), 0, st, c.v, nf);
+    return run_sweeps(c, Streamed{fine_op(c), c.ncx, c.ncy, c.diag, f, u, c.v}, nu, st);
 }
 
 }  // namespace sstep

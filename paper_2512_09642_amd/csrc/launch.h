@@ -246,6 +246,7 @@ struct CoarseArgs {
     const int32_t *order = nullptr;       // coarse unknowns by wavefront [n_c]
     const int32_t *wf = nullptr;          // wavefront starts [nwf + 1]
     int nwf = 0;
+    int max_front = 0;                    // unknowns of the largest wavefront
 };
 // a_jj and, when formed, the rows of A_c.
 hipError_t launch_coarse_prepare(const CoarseArgs &c, hipStream_t st);
