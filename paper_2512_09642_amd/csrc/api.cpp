@@ -137,19 +137,32 @@ sstep_status dalloc(sstep_ctx *ctx, T **p, size_t count)
 
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
-// Copies count elements from host or device memory into a fresh device buffer.
+// Copies count elements over dst: device arrays on the library's stream, which
+// has been made to wait for the caller's (order_after_user), host arrays
+// before returning.
+template <typename T>
+sstep_status overwrite_device(sstep_ctx *ctx, T *dst, const T *src, size_t count, int ptr_space)
+{
+    if (ptr_space)
+        HIPCHK(ctx, hipMemcpyAsync(dst, src, count * sizeof(T), hipMemcpyDeviceToDevice, ctx->stream));
+    else
+        HIPCHK(ctx, hipMemcpy(dst, src, count * sizeof(T), hipMemcpyHostToDevice));
+    return SSTEP_OK;
+}
+
+// The same into a fresh device buffer.
 template <typename T>
 sstep_status to_device(sstep_ctx *ctx, T **dst, const T *src, size_t count, int ptr_space)
 {
     OKCHK(dalloc(ctx, dst, count));
-    HIPCHK(ctx, hipMemcpy(*dst, src, count * sizeof(T), ptr_space ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice));
-    return SSTEP_OK;
+    return overwrite_device(ctx, *dst, src, count, ptr_space);
 }
 
-template <typename T>
-sstep_status overwrite_device(sstep_ctx *ctx, T *dst, const T *src, size_t count, int ptr_space)
+// The library's stream waits for what the caller's has been given so far.
+sstep_status order_after_user(sstep_ctx *ctx)
 {
-    HIPCHK(ctx, hipMemcpy(dst, src, count * sizeof(T), ptr_space ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice));
+    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
+    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
     return SSTEP_OK;
 }
 
@@ -214,6 +227,8 @@ sstep_status check_operator(sstep_ctx *ctx, const sstep_operator *A)
 // columns in range and strictly ascending within a row.
 sstep_status check_csr_pattern(sstep_ctx *ctx, const sstep_operator *A)
 {
+    if (A->ptr_space)  // the pattern is read here, by the host
+        HIPCHK(ctx, hipStreamSynchronize(static_cast<hipStream_t>(ctx->opt.stream)));
     hipError_t e1, e2;
     std::vector<int32_t> rp = to_host(A->row_ptr, size_t(A->n + 1), A->ptr_space, &e1);
     std::vector<int32_t> ci = to_host(A->col_idx, size_t(A->nnz), A->ptr_space, &e2);
@@ -476,8 +491,7 @@ sstep_status start_state(sstep_ctx *ctx, const double *b, double *x, double tol,
     h.no_stop = no_stop;
     h.max_outer = no_stop ? (1 << 30) : ctx->opt.max_outer;
     h.hist_cap = ctx->it.hist_cap;
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, hipMemcpyAsync(ctx->it.st, &h, sizeof(DevState), hipMemcpyHostToDevice, ctx->stream));
     if (ctx->it.fp32) {
         HIPCHK(ctx, launch_residual(ctx->it, ctx->stream, false));
@@ -848,6 +862,7 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_poll[1], hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
+    OKCHK(order_after_user(ctx));
     {
         void *p = nullptr;
         HIPCHK(ctx, hipHostMalloc(&p, sizeof(DevState), hipHostMallocDefault));
@@ -992,6 +1007,7 @@ sstep_status sstep_update_coefficients(sstep_ctx *ctx, const sstep_operator *A)
         if (op.kind == kOpPoisson || op.kind == kOpPoisson27)
             return SSTEP_OK;  // no coefficients
     }
+    OKCHK(order_after_user(ctx));
     return load_coefficients(ctx, A, false);
 }
 
@@ -1005,8 +1021,7 @@ sstep_status sstep_apply(sstep_ctx *ctx, const double *x, double *y)
         return SSTEP_E_ARG;
     if (!x || !y || x == y)
         return fail(ctx, SSTEP_E_ARG, "x and y must be distinct non-NULL device pointers");
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, launch_apply(ctx->it.op, x, y, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return SSTEP_OK;
@@ -1085,8 +1100,7 @@ sstep_status sstep_grad_operator(sstep_ctx *ctx, const double *lam, const double
         return fail(ctx, SSTEP_E_ARG, "lam, x and dA must not be NULL");
     if (ctx->it.op.kind == kOpPoisson27)
         return fail(ctx, SSTEP_E_UNSUPPORTED, "the 27-point operator has no coefficients to differentiate");
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, launch_grad(ctx->it.op, lam, x, dA, accumulate ? 1 : 0, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return SSTEP_OK;
@@ -1168,8 +1182,7 @@ sstep_status sstep_lanczos(sstep_ctx *ctx, const double *u, int32_t steps, doubl
             OKCHK(dalloc(ctx, &ctx->lz_vecs, size_t(3) * size_t(it.ld)));
         l.v[0] = ctx->lz_vecs, l.v[1] = ctx->lz_vecs + it.ld, l.v[2] = ctx->lz_vecs + 2 * it.ld;
     }
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, hipMemsetAsync(l.ls, 0, sizeof(LzState), ctx->stream));
     HIPCHK(ctx, hipMemsetAsync(l.ab, 0, size_t(3 * kMaxLanczos) * sizeof(double), ctx->stream));
     HIPCHK(ctx, launch_lanczos(l, it.op, u, steps, ctx->stream));
@@ -1517,6 +1530,7 @@ static sstep_status setup_batched_impl(sstep_ctx *ctx, int32_t nsys, const sstep
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_poll[1], hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
+    OKCHK(order_after_user(ctx));
     ctx->batch = new (std::nothrow) Batched();
     if (!ctx->batch)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");
@@ -1823,8 +1837,7 @@ sstep_status sstep_solve_batched(sstep_ctx *ctx, const double *const *b, double 
             h.max_outer = ctx->opt.max_outer;
         }
     *B.gl_host = BGlob{0, a.npairs};
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, hipMemcpyAsync(a.pairs, B.pairs_host, sizeof(DevState) * size_t(a.npairs), hipMemcpyHostToDevice,
                                ctx->stream));
     HIPCHK(ctx, hipMemcpyAsync(a.gl, B.gl_host, sizeof(BGlob), hipMemcpyHostToDevice, ctx->stream));
@@ -1914,6 +1927,7 @@ static sstep_status coarse_setup_impl(sstep_ctx *ctx, const sstep_operator *Af, 
     HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking));
     ctx->user = static_cast<hipStream_t>(ctx->opt.stream);
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming));
+    OKCHK(order_after_user(ctx));
     ctx->coarse = new (std::nothrow) CoarseArgs();
     if (!ctx->coarse)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");
@@ -1997,8 +2011,7 @@ sstep_status sstep_coarse_fgs(sstep_ctx *ctx, const double *f, double *u, int32_
         return fail(ctx, SSTEP_E_ARG, "f and u must be distinct non-NULL device pointers");
     if (nu < 0)
         return fail(ctx, SSTEP_E_ARG, "nu must be >= 0");
-    HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
-    HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    OKCHK(order_after_user(ctx));
     HIPCHK(ctx, launch_coarse_fgs(*ctx->coarse, f, u, nu, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return SSTEP_OK;
