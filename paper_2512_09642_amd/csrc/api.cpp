@@ -252,43 +252,63 @@ sstep_status check_csr_pattern(sstep_ctx *ctx, const sstep_operator *A)
     return SSTEP_OK;
 }
 
-// The sliced ELL copy of a CSR pattern (OpEll): slice widths from the
-// (validated) row pointers, slice offsets uploaded, columns filled on the
-// device; the values are filled by load_coefficients.
-sstep_status setup_ell(sstep_ctx *ctx, const sstep_operator *A)
+// The sliced copy of a CSR pattern (OpEll) from the device copy of the
+// (validated) pattern: the device counts each slice's longest row and its
+// offsets, the host lays the slices out, the device fills the pattern; the
+// values are filled by load_coefficients.
+sstep_status setup_ell(sstep_ctx *ctx)
 {
     OpDev &op = ctx->it.op;
-    hipError_t e = hipSuccess;
-    const std::vector<int32_t> rp = to_host(A->row_ptr, size_t(A->n + 1), A->ptr_space, &e);
-    if (e != hipSuccess)
-        return hip_fail(ctx, "hipMemcpy(row_ptr)", e);
     const int64_t nslice = (op.n + kEllSlice - 1) / kEllSlice;
-    std::vector<int64_t> off(size_t(nslice) + 1, 0);
+    int32_t *count = nullptr;  // widths, then offsets
+    OKCHK(dalloc(ctx, &count, 2 * size_t(nslice)));
+    HIPCHK(ctx, launch_ell_plan(op, nslice, count, count + nslice, ctx->stream));
+    std::vector<int32_t> h(2 * size_t(nslice));
+    HIPCHK(ctx, hipMemcpyAsync(h.data(), count, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    std::vector<EllSlice> slice(size_t(nslice), EllSlice{});
+    int64_t nval = 0, ncol = 0, noff = 0;
     for (int64_t q = 0; q < nslice; ++q) {
-        int32_t w = 0;
-        for (int64_t r = q * kEllSlice; r < std::min<int64_t>(op.n, (q + 1) * kEllSlice); ++r)
-            w = std::max(w, rp[size_t(r) + 1] - rp[size_t(r)]);
-        off[size_t(q) + 1] = off[size_t(q)] + int64_t(w) * kEllSlice;
+        EllSlice &S = slice[size_t(q)];
+        S.diag = h[size_t(nslice + q)] > 0;
+        S.w = S.diag ? h[size_t(nslice + q)] : h[size_t(q)];
+        S.val = nval;
+        S.pat = S.diag ? noff : ncol;
+        nval += int64_t(S.w) * kEllSlice;
+        if (S.diag)
+            noff += round_up(S.w, kEllGroup);
+        else
+            ncol += int64_t(S.w) * kEllSlice;
     }
-    const size_t total = size_t(off[size_t(nslice)]);
-    int64_t *doff = nullptr;
-    int32_t *col = nullptr;
+    EllSlice *dslice = nullptr;
+    int32_t *col = nullptr, *dofs = nullptr;
+    uint64_t *dmask = nullptr;
     double *val = nullptr;
-    OKCHK(dalloc(ctx, &doff, size_t(nslice) + 1));
-    OKCHK(dalloc(ctx, &col, total));
-    OKCHK(dalloc(ctx, &val, total));
-    HIPCHK(ctx, hipMemcpyAsync(doff, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
-    op.ell_off = doff;
+    OKCHK(dalloc(ctx, &dslice, size_t(nslice)));
+    OKCHK(dalloc(ctx, &col, size_t(ncol)));
+    OKCHK(dalloc(ctx, &dofs, size_t(noff)));
+    OKCHK(dalloc(ctx, &dmask, size_t(noff)));
+    OKCHK(dalloc(ctx, &val, size_t(nval)));
+    HIPCHK(ctx, hipMemcpyAsync(dslice, slice.data(), slice.size() * sizeof(EllSlice), hipMemcpyHostToDevice,
+                               ctx->stream));
+    op.ell_slice = dslice;
     op.ell_nslice = nslice;
+    op.ell_bytes = nval * int64_t(sizeof(double));
     op.ell_col = col;
     op.ell_val = val;
-    HIPCHK(ctx, launch_ell_fill_col(op, col, ctx->stream));
+    op.ell_dofs = dofs;
+    op.ell_dmask = dmask;
+    if (noff > 0) {
+        HIPCHK(ctx, hipMemsetAsync(dofs, 0, size_t(noff) * sizeof(int32_t), ctx->stream));
+        HIPCHK(ctx, hipMemsetAsync(dmask, 0, size_t(noff) * sizeof(uint64_t), ctx->stream));
+    }
+    HIPCHK(ctx, launch_ell_fill_pattern(op, col, dofs, dmask, ctx->stream));
     if (ctx->it.fp32) {
         float *val32 = nullptr;
-        OKCHK(dalloc(ctx, &val32, total));
+        OKCHK(dalloc(ctx, &val32, size_t(nval)));
         op.ell_val32 = val32;
     }
-    // off must stay alive until the copy has run
+    // slice must stay alive until the copy has run
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return SSTEP_OK;
 }
@@ -321,7 +341,7 @@ sstep_status load_coefficients(sstep_ctx *ctx, const sstep_operator *A, bool fir
         }
         HIPCHK(ctx, launch_diag_from_csr(op, dvec, bad, s));
         HIPCHK(ctx, launch_invert(dvec, invd, op.n, op.precond, s));
-        if (op.ell_col)
+        if (op.ell_slice)
             HIPCHK(ctx, launch_ell_fill_val(op, op.val, const_cast<double *>(op.ell_val), s));
         if (fp32) {
             float *val32 = const_cast<float *>(op.val32), *invd32 = const_cast<float *>(op.invd32);
@@ -453,8 +473,9 @@ void set_residual_schedule(IterArgs &it)
 {
     const OpDev &op = it.op;
     const int64_t n = op.n;
-    it.nbr = int(std::min<int64_t>(1024, (n + kBlock - 1) / kBlock));
-    it.rchunk = round_up((n + it.nbr - 1) / it.nbr, kBlock);
+    const int threads = residual_threads(n);
+    it.nbr = int(std::min<int64_t>(1024, (n + threads - 1) / threads));
+    it.rchunk = round_up((n + it.nbr - 1) / it.nbr, threads);
     it.res_m = 0;
     if (const int blocks = residual_march_blocks(op)) {
         it.res_m = 1;
@@ -902,7 +923,7 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
         op.rp = rp;
         op.ci = ci;
         ctx->grad_size = A->nnz;
-        OKCHK(setup_ell(ctx, A));
+        OKCHK(setup_ell(ctx));
     }
     it.ld = round_up(op.n, kPad);
     OKCHK(load_coefficients(ctx, A, true));

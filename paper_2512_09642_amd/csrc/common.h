@@ -260,25 +260,47 @@ struct OpCsr {
     }
 };
 
-// The same CSR operator stored as sliced ELL: rows in slices of kEllSlice
-// consecutive rows; slice q holds w_q = (off[q+1] - off[q]) / kEllSlice
-// entries per row (the longest row of the slice), column-major inside the
-// slice, so entry k of row r = q kEllSlice + l sits at off[q] + k kEllSlice +
-// l and the lanes of a wave that takes one slice read each entry index with
-// one coalesced load.  A row keeps its CSR entries in their order; the
-// padding has column -1 and is skipped, so the sum is formed with the same
-// operations in the same order as by OpCsr.
+// The same CSR operator stored in slices of kEllSlice consecutive rows, one
+// wave a slice, values column-major inside the slice, so the lanes of a wave
+// read each entry index with one coalesced load.  A row keeps its CSR entries
+// in their order, so the sum is formed with the same operations in the same
+// order as by OpCsr.  A slice comes in one of two forms:
+//  * listed (EllSlice::diag 0): as many entries per row as the longest row of
+//    the slice has, each with its column; the padding has column -1 and is
+//    skipped;
+//  * by offsets (diag 1): the distinct values of column - row in the slice,
+//    ascending, each with the bit mask of the rows that have such an entry;
+//    no column is stored or read (8 bytes an entry instead of 12), and the
+//    addresses of the vector do not wait for a column.  Matrices from grids
+//    have few offsets.  Chosen per slice where the offsets times 7 are at
+//    most the longest row times 10 (the bytes of both forms are then equal in
+//    FP64; rows missing an offset hold a zero there that is not used).
 constexpr int kEllSlice = 64;
-//
+constexpr int kEllGroup = 8;  // offsets of a slice are padded to a multiple of this
+
+struct EllSlice {
+    int64_t val;   // first value (w times kEllSlice follow)
+    int64_t pat;   // first column (listed) or first offset and mask
+    int32_t w;     // entries per row (listed) or offsets
+    int32_t diag;
+};
+
 // In FP64 the Jacobi weight is formed from the row's own diagonal entry,
 // precond ? 1 / a_cc : 1 (the value the M^{-1} vector holds, to the bit),
 // which saves reading that vector; FP32 reads its rounded copy.
-template <typename T>
+//
+// Called by the lanes of a wave with consecutive c from a multiple of
+// kEllSlice on; a lane past the last row may repeat the last row, and then
+// gets a value of no meaning.
+template <typename T, bool KEEP>
 struct OpEll {
+    const EllSlice *__restrict__ slice;
     const int32_t *__restrict__ col;
     const T *__restrict__ val;
-    const int64_t *__restrict__ off;
+    const int32_t *__restrict__ dofs;
+    const uint64_t *__restrict__ dmask;
     const T *__restrict__ invd;  // M^{-1} diagonal (all ones without preconditioning); FP32 only
+    int32_t n;
     int precond;
 
     __device__ __forceinline__ void apply(const T *__restrict__ p, int64_t c, T &pc, T &y, T &dinv) const
@@ -286,30 +308,79 @@ struct OpEll {
         T wt;
         apply_w(p, c, pc, y, dinv, wt);
     }
+    // A matrix entry: through the caches (KEEP) or, read once per product,
+    // non-temporal.
+    template <typename V>
+    static __device__ __forceinline__ V entry(const V *q)
+    {
+        if constexpr (KEEP)
+            return *q;
+        else
+            return __builtin_nontemporal_load(q);
+    }
     __device__ __forceinline__ void apply_w(const T *__restrict__ p, int64_t c, T &pc, T &y, T &dinv, T &wt) const
     {
-        const int64_t q = c / kEllSlice;
-        const int64_t o0 = off[q];
-        const int w = static_cast<int>((off[q + 1] - o0) / kEllSlice);
-        const int64_t b = o0 + (c - q * kEllSlice);
+        const int32_t row = static_cast<int32_t>(c);
+        const int32_t q = __builtin_amdgcn_readfirstlane(row / kEllSlice);
+        const EllSlice S = slice[q];
+        const T *__restrict__ v = val + S.val + (row - q * kEllSlice);
         T acc = T(0), diag = T(1);
-        constexpr int U = 8;  // entries whose loads are issued together
-        for (int k0 = 0; k0 < w; k0 += U) {
+        constexpr int U = kEllGroup;  // entries whose loads are issued together
+        if (S.diag) {
+            const int32_t *__restrict__ off = dofs + S.pat;
+            const uint64_t *__restrict__ mask = dmask + S.pat;
+            // offsets and masks are padded to a multiple of U (mask 0); the
+            // values of the padding repeat the last ones
+            for (int k0 = 0; k0 < S.w; k0 += U) {
+                T a[U], x[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int k = k0 + u < S.w ? k0 + u : S.w - 1;
+                    a[u] = entry(v + int64_t(k) * kEllSlice);
+                    const int32_t j = row + off[k0 + u];
+                    x[u] = p[j < 0 ? 0 : (j < n ? j : n - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint64_t m = mask[k0 + u];
+                    acc += a[u] * (__builtin_amdgcn_inverse_ballot_w64(m) ? x[u] : T(0));
+                    diag = __builtin_amdgcn_inverse_ballot_w64(off[k0 + u] == 0 ? m : 0) ? a[u] : diag;
+                }
+            }
+        } else {
+            const int32_t *__restrict__ cp = col + S.pat + (row - q * kEllSlice);
+            // the columns and values of the next U entries are in flight while
+            // the vector's entries of these are (30011 random rows of 46: 18.8
+            // -> 15 us; 16 entries at a time take registers from the other form)
             int32_t j[U];
-            T v[U];
+            T a[U];
+            auto fetch = [&](int k0, int32_t(&jj)[U], T(&aa)[U]) {
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (k0 + u < w) {  // read once per product: non-temporal
-                    j[u] = __builtin_nontemporal_load(col + b + int64_t(k0 + u) * kEllSlice);
-                    v[u] = __builtin_nontemporal_load(val + b + int64_t(k0 + u) * kEllSlice);
+                for (int u = 0; u < U; ++u) {
+                    jj[u] = -1;
+                    aa[u] = T(0);
+                    if (k0 + u < S.w) {
+                        jj[u] = entry(cp + int64_t(k0 + u) * kEllSlice);
+                        aa[u] = entry(v + int64_t(k0 + u) * kEllSlice);
+                    }
                 }
+            };
+            fetch(0, j, a);
+            for (int k0 = 0; k0 < S.w; k0 += U) {
+                T x[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (k0 + u < w && j[u] >= 0) {
-                    acc += v[u] * p[j[u]];
-                    if (j[u] == c)
-                        diag = v[u];
+                for (int u = 0; u < U; ++u)
+                    x[u] = p[j[u] >= 0 ? j[u] : row];
+                int32_t jn[U];
+                T an[U];
+                fetch(k0 + U, jn, an);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    acc = j[u] >= 0 ? acc + a[u] * x[u] : acc;
+                    diag = j[u] == row ? a[u] : diag;
+                    j[u] = jn[u], a[u] = an[u];
                 }
+            }
         }
         pc = p[c];
         y = acc;

@@ -19,10 +19,19 @@ struct Launch1D {
 
 inline uint32_t blocks_for(int64_t n) { return static_cast<uint32_t>((n + kBlock - 1) / kBlock); }
 
-Launch1D plan_points(int64_t n)
+// Threads per block of the kernels with a thread per point: one wave up to
+// this many unknowns, so that the waves of a small system spread over as many
+// CUs as there are and a block's sums need no barrier.  Basis step of a random
+// matrix of 30011 rows (46 gathers a row through each CU's own cache port) 11.6
+// -> 8.9 us, 7-point CSR 16^3 3.9 -> 3.5; equal from 40^3 on, where the
+// residual's 1024 blocks of one wave are slower (5.8 -> 7.4 us).
+constexpr int64_t kWaveBlocksMax = 32768;
+inline int point_threads(int64_t n) { return n <= kWaveBlocksMax ? kWave : kBlock; }
+
+Launch1D plan_points(int64_t n, int threads = kBlock)
 {
     Launch1D l;
-    l.nbl = static_cast<uint32_t>((n + kBlock - 1) / kBlock);
+    l.nbl = static_cast<uint32_t>((n + threads - 1) / threads);
     l.per = (l.nbl + kNumXcd - 1) / kNumXcd;
     l.grid = l.per * kNumXcd;
     return l;
@@ -62,8 +71,8 @@ __global__ __launch_bounds__(kSumThreads) void k_stop(DevState *__restrict__ st,
 
 // r = b - A x in FP64, partial sums of r^2 per logical block, and the basis
 // start p_0 = p0scale * (M^{-1} r or r) written as column 0 of P.
-template <class Op, typename TP>
-__global__ __launch_bounds__(kBlock) void k_residual(const DevState *__restrict__ st, Op op, TP *__restrict__ p0,
+template <class Op, typename TP, int NT>
+__global__ __launch_bounds__(NT) void k_residual(const DevState *__restrict__ st, Op op, TP *__restrict__ p0,
                                                      double *__restrict__ rpart, int64_t n, int64_t chunk,
                                                      uint32_t per, uint32_t nbl, int p0_mode, int write_p0)
 {
@@ -78,7 +87,7 @@ __global__ __launch_bounds__(kBlock) void k_residual(const DevState *__restrict_
     const int64_t beg = static_cast<int64_t>(lb) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
     double acc = 0.0;
-    for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
+    for (int64_t c = beg + threadIdx.x; c < end; c += NT) {
         double pc, y, dinv;
         op.apply(x, c, pc, y, dinv);
         const double r = __builtin_nontemporal_load(b + c) - y;  // b is read once
@@ -86,7 +95,8 @@ __global__ __launch_bounds__(kBlock) void k_residual(const DevState *__restrict_
         if (write_p0)
             p0[c] = static_cast<TP>(scale * (p0_mode ? r : dinv * r));
     }
-    block_sum_store(acc, rpart + lb);
+    const double v[1] = {acc};
+    block_partials<1, NT>(v, rpart + lb, 1);
 }
 
 // One step of the Chebyshev recurrence fused with the operator apply
@@ -95,8 +105,8 @@ __global__ __launch_bounds__(kBlock) void k_residual(const DevState *__restrict_
 //   p_1     = theta (M^{-1} y - sigma p_0)            (STEP 0, j = 0)
 //   p_{j+1} = 2 theta (M^{-1} y - sigma p_j) - p_{j-1} (STEP 1, 0 < j < s-1)
 //   nothing more for j = s-1                          (STEP 2)
-template <class Op, typename T, int STEP>
-__global__ __launch_bounds__(kBlock) void k_basis(const DevState *__restrict__ st, Op op, const T *__restrict__ pj,
+template <class Op, typename T, int STEP, int NT>
+__global__ __launch_bounds__(NT) void k_basis(const DevState *__restrict__ st, Op op, const T *__restrict__ pj,
                                                   const T *__restrict__ pprev, T *__restrict__ apj,
                                                   T *__restrict__ pnext, T theta, T sigma, int64_t n, uint32_t per,
                                                   uint32_t nbl)
@@ -106,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_basis(const DevState *__restrict__ s
     const uint32_t lb = xcd_block(blockIdx.x, per);
     if (lb >= nbl)
         return;
-    const int64_t c = static_cast<int64_t>(lb) * kBlock + threadIdx.x;
+    const int64_t c = static_cast<int64_t>(lb) * NT + threadIdx.x;
     if (c >= n)
         return;
     T pc, y, dinv;
@@ -127,8 +137,8 @@ __global__ __launch_bounds__(kBlock) void k_basis(const DevState *__restrict__ s
 // first when j = 0, written to consecutive slots of mpart (stride mstride),
 // one value per logical block.  The threads past n take part in the block
 // sums with weight 0.
-template <class Op, typename T, int STEP>
-__global__ __launch_bounds__(kBlock) void k_basis_mom(const DevState *__restrict__ st, Op op,
+template <class Op, typename T, int STEP, int NT>
+__global__ __launch_bounds__(NT) void k_basis_mom(const DevState *__restrict__ st, Op op,
                                                       const T *__restrict__ pj, const T *__restrict__ pprev,
                                                       T *__restrict__ pnext, T theta, T sigma, int64_t n,
                                                       uint32_t per, uint32_t nbl, double *__restrict__ mpart,
@@ -140,7 +150,7 @@ __global__ __launch_bounds__(kBlock) void k_basis_mom(const DevState *__restrict
     const uint32_t lb = xcd_block(blockIdx.x, per);
     if (lb >= nbl)
         return;  // whole block
-    const int64_t c = static_cast<int64_t>(lb) * kBlock + threadIdx.x;
+    const int64_t c = static_cast<int64_t>(lb) * NT + threadIdx.x;
     const bool valid = c < n;
     const int64_t cc = valid ? c : n - 1;
     T pc, y, dinv, wt;
@@ -156,10 +166,10 @@ __global__ __launch_bounds__(kBlock) void k_basis_mom(const DevState *__restrict
     const double a = static_cast<double>(pn), b = static_cast<double>(pc);
     if constexpr (STEP == 0) {
         const double v[3] = {w * b * b, w * a * b, w * a * a};
-        block_partials<3, kBlock>(v, mpart + lb, mstride);
+        block_partials<3, NT>(v, mpart + lb, mstride);
     } else {
         const double v[2] = {w * a * b, w * a * a};
-        block_partials<2, kBlock>(v, mpart + lb, mstride);
+        block_partials<2, NT>(v, mpart + lb, mstride);
     }
 }
 
@@ -486,14 +496,21 @@ __global__ __launch_bounds__(kBlock) void k_invert(const double *__restrict__ sr
 
 
 
-template <class Op, typename TP>
-hipError_t residual_for(const IterArgs &a, const Op &op, hipStream_t st, bool write_p0)
+template <class Op, typename TP, int NT>
+hipError_t residual_for_nt(const IterArgs &a, const Op &op, hipStream_t st, bool write_p0)
 {
     const uint32_t per = (static_cast<uint32_t>(a.nbr) + kNumXcd - 1) / kNumXcd;
-    hipLaunchKernelGGL((k_residual<Op, TP>), dim3(per * kNumXcd), dim3(kBlock), 0, st, a.st, op,
+    hipLaunchKernelGGL((k_residual<Op, TP, NT>), dim3(per * kNumXcd), dim3(NT), 0, st, a.st, op,
                        static_cast<TP *>(a.P), a.rpart, a.op.n, a.rchunk, per, static_cast<uint32_t>(a.nbr),
                        a.p0_mode, write_p0 ? 1 : 0);
     return hipGetLastError();
+}
+
+template <class Op, typename TP>
+hipError_t residual_for(const IterArgs &a, const Op &op, hipStream_t st, bool write_p0)
+{
+    return point_threads(a.op.n) == kWave ? residual_for_nt<Op, TP, kWave>(a, op, st, write_p0)
+                                          : residual_for_nt<Op, TP, kBlock>(a, op, st, write_p0);
 }
 
 // Where a marched kernel (march.h) takes the place of one point per thread.
@@ -545,8 +562,10 @@ hipError_t residual_t(const IterArgs &a, hipStream_t st, bool write_p0)
     case kOpPoisson27:
         return residual_for<OpPoisson27<double>, TP>(a, make_poisson27<double>(a.op), st, write_p0);
     default:
-        if (a.op.ell_col)
-            return residual_for<OpEll<double>, TP>(a, Ops<double>::ell(a.op), st, write_p0);
+        if (a.op.ell_slice)
+            return ell_keep(a.op, 8)
+                       ? residual_for<OpEll<double, true>, TP>(a, Ops<double>::ell<true>(a.op), st, write_p0)
+                       : residual_for<OpEll<double, false>, TP>(a, Ops<double>::ell<false>(a.op), st, write_p0);
         return residual_for<OpCsr<double>, TP>(a, Ops<double>::csr(a.op), st, write_p0);
     }
 }
@@ -584,10 +603,10 @@ hipError_t basis_march(const IterArgs &a, int j, int step, hipStream_t st)
     return hipGetLastError();
 }
 
-template <class Op, typename T>
-hipError_t basis_for(const IterArgs &a, const Op &op, int j, int step, hipStream_t st)
+template <class Op, typename T, int NT>
+hipError_t basis_for_nt(const IterArgs &a, const Op &op, int j, int step, hipStream_t st)
 {
-    const Launch1D l = plan_points(a.op.n);
+    const Launch1D l = plan_points(a.op.n, NT);
     T *P = static_cast<T *>(a.P);
     T *AP = static_cast<T *>(a.AP);
     const T *pj = P + j * a.ld;
@@ -600,23 +619,30 @@ hipError_t basis_for(const IterArgs &a, const Op &op, int j, int step, hipStream
             return hipErrorInvalidValue;
         double *mp = a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride;
         if (step == 0)
-            hipLaunchKernelGGL((k_basis_mom<Op, T, 0>), dim3(l.grid), dim3(kBlock), 0, st, a.st, op, pj, pprev,
+            hipLaunchKernelGGL((k_basis_mom<Op, T, 0, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev,
                                pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride);
         else
-            hipLaunchKernelGGL((k_basis_mom<Op, T, 1>), dim3(l.grid), dim3(kBlock), 0, st, a.st, op, pj, pprev,
+            hipLaunchKernelGGL((k_basis_mom<Op, T, 1, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev,
                                pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride);
         return hipGetLastError();
     }
     if (step == 2)
-        hipLaunchKernelGGL((k_basis<Op, T, 2>), dim3(l.grid), dim3(kBlock), 0, st, a.st, op, pj, pprev, apj, pnext,
+        hipLaunchKernelGGL((k_basis<Op, T, 2, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev, apj, pnext,
                            theta, sigma, a.op.n, l.per, l.nbl);
     else if (step == 0)
-        hipLaunchKernelGGL((k_basis<Op, T, 0>), dim3(l.grid), dim3(kBlock), 0, st, a.st, op, pj, pprev, apj, pnext,
+        hipLaunchKernelGGL((k_basis<Op, T, 0, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev, apj, pnext,
                            theta, sigma, a.op.n, l.per, l.nbl);
     else
-        hipLaunchKernelGGL((k_basis<Op, T, 1>), dim3(l.grid), dim3(kBlock), 0, st, a.st, op, pj, pprev, apj, pnext,
+        hipLaunchKernelGGL((k_basis<Op, T, 1, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev, apj, pnext,
                            theta, sigma, a.op.n, l.per, l.nbl);
     return hipGetLastError();
+}
+
+template <class Op, typename T>
+hipError_t basis_for(const IterArgs &a, const Op &op, int j, int step, hipStream_t st)
+{
+    return point_threads(a.op.n) == kWave ? basis_for_nt<Op, T, kWave>(a, op, j, step, st)
+                                          : basis_for_nt<Op, T, kBlock>(a, op, j, step, st);
 }
 
 // FP64 constant Poisson with an even x-extent: pairs of points, two planes.
@@ -686,8 +712,10 @@ hipError_t basis_t(const IterArgs &a, int j, int step, hipStream_t st)
     case kOpPoisson27:
         return basis_for<OpPoisson27<T>, T>(a, make_poisson27<T>(a.op), j, step, st);
     default:
-        if (a.op.ell_col)
-            return basis_for<OpEll<T>, T>(a, Ops<T>::ell(a.op), j, step, st);
+        if (a.op.ell_slice)
+            return ell_keep(a.op, sizeof(T))
+                       ? basis_for<OpEll<T, true>, T>(a, Ops<T>::template ell<true>(a.op), j, step, st)
+                       : basis_for<OpEll<T, false>, T>(a, Ops<T>::template ell<false>(a.op), j, step, st);
         return basis_csr<T>(a, j, step, st);
     }
 }
@@ -757,39 +785,106 @@ hipError_t basis_pair(const IterArgs &a, int j, hipStream_t st)
     return f2_box(a) ? basis_pair_v<T, true, false>(a, j, st) : basis_pair_v<T, false, false>(a, j, st);
 }
 
-// Sliced ELL from CSR (OpEll, common.h): one thread per row slot of every
-// slice (rows at or beyond n are all padding).
-__global__ __launch_bounds__(kBlock) void k_ell_fill_col(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
-                                                        const int64_t *__restrict__ off, int64_t n, int64_t nslice,
-                                                        int32_t *__restrict__ col)
+// The sliced form of a CSR operator (OpEll, common.h), one wave a slice.
+// The offsets of a slice in ascending order are a merge of its rows: every
+// lane walks its row, and each step takes the smallest next column - row of
+// the wave.
+__device__ __forceinline__ int32_t wave_min(int32_t v)
 {
-    const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (r >= nslice * kEllSlice)
-        return;
-    const int64_t q = r / kEllSlice;
-    const int64_t b = off[q] + (r - q * kEllSlice);
-    const int w = static_cast<int>((off[q + 1] - off[q]) / kEllSlice);
-    const int32_t k0 = r < n ? rp[r] : 0;
-    const int len = r < n ? rp[r + 1] - k0 : 0;
-    for (int k = 0; k < w; ++k)
-        col[b + int64_t(k) * kEllSlice] = k < len ? ci[k0 + k] : -1;
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) {
+        const int32_t o = __shfl_xor(v, off, kWave);
+        v = o < v ? o : v;
+    }
+    return v;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_ell_fill_val(const int32_t *__restrict__ rp, const T *__restrict__ val,
-                                                        const int64_t *__restrict__ off, int64_t n, int64_t nslice,
-                                                        T *__restrict__ ev)
+// f(step, offset, has): has tells whether the lane's row holds the offset;
+// at most limit steps.  Returns the steps the whole slice takes, limit + 1 if
+// it takes more.
+template <class F>
+__device__ __forceinline__ int ell_merge(const int32_t *__restrict__ ci, int32_t row, int32_t k, int32_t end,
+                                         int limit, F &&f)
+{
+    constexpr int32_t kNone = 0x7fffffff;  // above every offset
+    for (int step = 0;; ++step) {
+        const int32_t own = k < end ? ci[k] - row : kNone;
+        const int32_t off = wave_min(own);
+        if (off == kNone || step > limit)
+            return step;
+        const bool has = own == off;
+        if (step < limit)
+            f(step, off, has);
+        k += has;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_ell_plan(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
+                                                    int64_t n, int64_t nslice, int32_t *__restrict__ width,
+                                                    int32_t *__restrict__ offsets)
 {
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (r >= nslice * kEllSlice)
-        return;
     const int64_t q = r / kEllSlice;
-    const int64_t b = off[q] + (r - q * kEllSlice);
-    const int w = static_cast<int>((off[q + 1] - off[q]) / kEllSlice);
-    const int32_t k0 = r < n ? rp[r] : 0;
-    const int len = r < n ? rp[r + 1] - k0 : 0;
-    for (int k = 0; k < w; ++k)
-        ev[b + int64_t(k) * kEllSlice] = k < len ? val[k0 + k] : T(0);
+    if (q >= nslice)
+        return;  // whole wave
+    const int32_t k0 = r < n ? rp[r] : 0, k1 = r < n ? rp[r + 1] : 0;
+    const int32_t w = -wave_min(-(k1 - k0));
+    const int limit = static_cast<int>(int64_t(w) * 10 / 7);
+    const int nd = ell_merge(ci, static_cast<int32_t>(r), k0, k1, limit, [](int, int32_t, bool) {});
+    if (threadIdx.x % kWave == 0) {
+        width[q] = w;
+        offsets[q] = nd <= limit ? nd : 0;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_ell_fill_pattern(const int32_t *__restrict__ rp,
+                                                            const int32_t *__restrict__ ci,
+                                                            const EllSlice *__restrict__ slice, int64_t n,
+                                                            int64_t nslice, int32_t *__restrict__ col,
+                                                            int32_t *__restrict__ dofs,
+                                                            uint64_t *__restrict__ dmask)
+{
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const int64_t q = r / kEllSlice;
+    if (q >= nslice)
+        return;  // whole wave
+    const int lane = threadIdx.x % kWave;
+    const EllSlice S = slice[q];
+    const int32_t k0 = r < n ? rp[r] : 0, k1 = r < n ? rp[r + 1] : 0;
+    if (S.diag) {
+        ell_merge(ci, static_cast<int32_t>(r), k0, k1, S.w, [&](int step, int32_t off, bool has) {
+            const uint64_t m = __ballot(has);
+            if (lane == 0) {
+                dofs[S.pat + step] = off;
+                dmask[S.pat + step] = m;
+            }
+        });
+    } else {
+        for (int k = 0; k < S.w; ++k)
+            col[S.pat + int64_t(k) * kEllSlice + lane] = k < k1 - k0 ? ci[k0 + k] : -1;
+    }
+}
+
+// One thread per row slot of every slice (rows at or beyond n hold nothing).
+template <typename T>
+__global__ __launch_bounds__(kBlock) void k_ell_fill_val(const int32_t *__restrict__ rp, const T *__restrict__ val,
+                                                        const EllSlice *__restrict__ slice,
+                                                        const uint64_t *__restrict__ dmask, int64_t n,
+                                                        int64_t nslice, T *__restrict__ ev)
+{
+    const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    const int64_t q = r / kEllSlice;
+    if (q >= nslice)
+        return;
+    const int lane = threadIdx.x % kWave;
+    const EllSlice S = slice[q];
+    int32_t k = r < n ? rp[r] : 0;
+    const int32_t end = r < n ? rp[r + 1] : 0;
+    for (int e = 0; e < S.w; ++e) {
+        const bool has = S.diag ? (dmask[S.pat + e] >> lane) & 1 : k < end;
+        ev[S.val + int64_t(e) * kEllSlice + lane] = has ? val[k] : T(0);
+        k += has;
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill_zero(uint64_t *__restrict__ p, int64_t words)
@@ -849,28 +944,36 @@ __global__ __launch_bounds__(kBlock) void k_check_csr_cols(const int32_t *__rest
 
 }  // namespace
 
-hipError_t launch_ell_fill_col(const OpDev &op, int32_t *col, hipStream_t st)
+hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, hipStream_t st)
 {
-    const uint32_t grid = blocks_for(op.ell_nslice * kEllSlice);
-    hipLaunchKernelGGL(k_ell_fill_col, dim3(grid), dim3(kBlock), 0, st, op.rp, op.ci, op.ell_off, op.n,
-                       op.ell_nslice, col);
+    hipLaunchKernelGGL(k_ell_plan, dim3(blocks_for(nslice * kEllSlice)), dim3(kBlock), 0, st, op.rp, op.ci, op.n,
+                       nslice, width, offsets);
+    return hipGetLastError();
+}
+
+hipError_t launch_ell_fill_pattern(const OpDev &op, int32_t *col, int32_t *dofs, uint64_t *dmask, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_ell_fill_pattern, dim3(blocks_for(op.ell_nslice * kEllSlice)), dim3(kBlock), 0, st, op.rp,
+                       op.ci, op.ell_slice, op.n, op.ell_nslice, col, dofs, dmask);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t ell_fill_val(const OpDev &op, const T *val, T *ev, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_ell_fill_val<T>, dim3(blocks_for(op.ell_nslice * kEllSlice)), dim3(kBlock), 0, st, op.rp,
+                       val, op.ell_slice, op.ell_dmask, op.n, op.ell_nslice, ev);
     return hipGetLastError();
 }
 
 hipError_t launch_ell_fill_val(const OpDev &op, const double *val, double *ev, hipStream_t st)
 {
-    const uint32_t grid = blocks_for(op.ell_nslice * kEllSlice);
-    hipLaunchKernelGGL(k_ell_fill_val<double>, dim3(grid), dim3(kBlock), 0, st, op.rp, val, op.ell_off, op.n,
-                       op.ell_nslice, ev);
-    return hipGetLastError();
+    return ell_fill_val(op, val, ev, st);
 }
 
 hipError_t launch_ell_fill_val(const OpDev &op, const float *val, float *ev, hipStream_t st)
 {
-    const uint32_t grid = blocks_for(op.ell_nslice * kEllSlice);
-    hipLaunchKernelGGL(k_ell_fill_val<float>, dim3(grid), dim3(kBlock), 0, st, op.rp, val, op.ell_off, op.n,
-                       op.ell_nslice, ev);
-    return hipGetLastError();
+    return ell_fill_val(op, val, ev, st);
 }
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st)
@@ -900,6 +1003,8 @@ hipError_t launch_check_csr_cols(const int32_t *rp, const int32_t *ci, int64_t n
     hipLaunchKernelGGL(k_check_csr_cols, dim3(blocks_for(n)), dim3(kBlock), 0, st, rp, ci, n, bad);
     return hipGetLastError();
 }
+
+int residual_threads(int64_t n) { return point_threads(n); }
 
 int residual_march_blocks(const OpDev &op)
 {
@@ -990,7 +1095,7 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
     const int elem = a.fp32 ? 4 : 8;
     const int64_t single = march_step(a.op, elem)
                                ? plan_march(a.op.g, a.op.kind == kOpPoisson27, elem).nbl
-                               : plan_points(a.op.n).nbl;
+                               : plan_points(a.op.n, point_threads(a.op.n)).nbl;
     for (; j < m; ++j)
         put(j, 1, single);
     *stride = mx;
@@ -1032,9 +1137,12 @@ hipError_t launch_apply(const OpDev &op, const double *x, double *y, hipStream_t
                            make_poisson27<double>(op), x, y, op.n, l.per, l.nbl);
         break;
     default:
-        if (op.ell_col)
-            hipLaunchKernelGGL(k_apply<OpEll<double>>, dim3(l.grid), dim3(kBlock), 0, st, Ops<double>::ell(op), x,
-                               y, op.n, l.per, l.nbl);
+        if (op.ell_slice && ell_keep(op, 8))
+            hipLaunchKernelGGL((k_apply<OpEll<double, true>>), dim3(l.grid), dim3(kBlock), 0, st,
+                               Ops<double>::ell<true>(op), x, y, op.n, l.per, l.nbl);
+        else if (op.ell_slice)
+            hipLaunchKernelGGL((k_apply<OpEll<double, false>>), dim3(l.grid), dim3(kBlock), 0, st,
+                               Ops<double>::ell<false>(op), x, y, op.n, l.per, l.nbl);
         else
             hipLaunchKernelGGL(k_apply<OpCsr<double>>, dim3(l.grid), dim3(kBlock), 0, st, Ops<double>::csr(op), x,
                                y, op.n, l.per, l.nbl);

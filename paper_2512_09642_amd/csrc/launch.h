@@ -42,12 +42,15 @@ struct OpDev {
     const float *invd32 = nullptr;
     const double *dvec = nullptr;  // M diagonal (Jacobi, non-constant diagonal)
     const float *dvec32 = nullptr;
-    // CSR also stored as sliced ELL (OpEll, common.h) when ell_col is set
-    const int32_t *ell_col = nullptr;
+    // CSR also stored in slices (OpEll, common.h) when ell_slice is set
+    const EllSlice *ell_slice = nullptr;  // [ell_nslice]
+    const int32_t *ell_col = nullptr;     // columns of the listed slices
     const double *ell_val = nullptr;
     const float *ell_val32 = nullptr;
-    const int64_t *ell_off = nullptr;  // [nslice + 1]
+    const int32_t *ell_dofs = nullptr;    // offsets and row masks of the others
+    const uint64_t *ell_dmask = nullptr;
     int64_t ell_nslice = 0;
+    int64_t ell_bytes = 0;                // bytes of the values in FP64
 };
 
 // Everything one outer iteration needs; all pointers are device memory.
@@ -257,11 +260,15 @@ hipError_t launch_residual(const IterArgs &a, hipStream_t st, bool write_p0);
 // Blocks (= partials) of the marched residual of a constant operator, 0 where
 // it does not serve the operator.
 int residual_march_blocks(const OpDev &op);
+// Threads per block of the other residual kernels.
+int residual_threads(int64_t n);
 hipError_t launch_p0scale(const IterArgs &a, hipStream_t st);
 hipError_t launch_basis(const IterArgs &a, int j, hipStream_t st);
-// Sliced ELL copy of a CSR operator: the columns (pattern) and the values in
-// FP64 or FP32 (from the CSR arrays rp, ci, val of the same precision).
-hipError_t launch_ell_fill_col(const OpDev &op, int32_t *col, hipStream_t st);
+// Sliced copy of a CSR operator (OpEll): per slice the longest row and the
+// offsets (0: too many, the slice is listed); the pattern; the values in FP64
+// or FP32 (from the CSR arrays rp, ci, val of the same precision).
+hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, hipStream_t st);
+hipError_t launch_ell_fill_pattern(const OpDev &op, int32_t *col, int32_t *dofs, uint64_t *dmask, hipStream_t st);
 hipError_t launch_ell_fill_val(const OpDev &op, const double *val, double *ev, hipStream_t st);
 hipError_t launch_ell_fill_val(const OpDev &op, const float *val, float *ev, hipStream_t st);
 // The whole basis p_1 .. p_m of one outer iteration: two steps per launch

@@ -24,13 +24,30 @@ template <>
 struct Ops<double> {
     static OpFaces7<double> faces(const OpDev &op) { return {op.g, op.kx, op.ky, op.kz, op.precond}; }
     static OpCsr<double> csr(const OpDev &op) { return {op.rp, op.ci, op.val, op.invd}; }
-    static OpEll<double> ell(const OpDev &op) { return {op.ell_col, op.ell_val, op.ell_off, nullptr, op.precond}; }
+    template <bool KEEP>
+    static OpEll<double, KEEP> ell(const OpDev &op)
+    {
+        return {op.ell_slice, op.ell_col, op.ell_val, op.ell_dofs, op.ell_dmask, nullptr, static_cast<int32_t>(op.n),
+                op.precond};
+    }
 };
 template <>
 struct Ops<float> {
     static OpFaces7<float> faces(const OpDev &op) { return {op.g, op.kx32, op.ky32, op.kz32, op.precond}; }
     static OpCsr<float> csr(const OpDev &op) { return {op.rp, op.ci, op.val32, op.invd32}; }
-    static OpEll<float> ell(const OpDev &op) { return {op.ell_col, op.ell_val32, op.ell_off, op.invd32, op.precond}; }
+    template <bool KEEP>
+    static OpEll<float, KEEP> ell(const OpDev &op)
+    {
+        return {op.ell_slice, op.ell_col, op.ell_val32, op.ell_dofs, op.ell_dmask, op.invd32,
+                static_cast<int32_t>(op.n), op.precond};
+    }
 };
+
+// Matrix values of at most this many bytes go through the caches, which hold
+// them between products: basis step of a 7-point matrix, FP64, cached against
+// non-temporal: 101^3 15.2 / 17.5 us, 128^3 (134 MB with padding) 28.4 / 35.7,
+// 160^3 (257 MB) 65.3 / 65.4, 192^3 126 / 109.
+constexpr int64_t kEllKeepBytes = int64_t(192) << 20;
+inline bool ell_keep(const OpDev &op, int elem) { return op.ell_bytes / 8 * elem <= kEllKeepBytes; }
 
 }  // namespace sstep
