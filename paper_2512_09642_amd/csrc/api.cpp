@@ -40,8 +40,8 @@ struct sstep_ctx {
     IterArgs it;
     sstep_options opt{};
     std::vector<void *> dev_allocs;
-    DevState *st_host = nullptr;  // pinned host mirror of the device state
-    int32_t *poll_host = nullptr; // pinned [2][4]: done, status, iter of the last replays
+    DevState *st_host = nullptr;  // pinned [2]: the device state after the last replays
+    int32_t *poll_host = nullptr; // pinned [2][4], batched: the global counters after the last replays
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     int chunk = 4;
@@ -502,8 +502,7 @@ hipError_t enqueue_iteration(const IterArgs &a, hipStream_t s)
 // Initial device state for a solve (or a single step) on b, x.
 sstep_status start_state(sstep_ctx *ctx, const double *b, double *x, double tol, int no_stop)
 {
-    DevState &h = *ctx->st_host;
-    std::memset(&h, 0, sizeof(DevState));
+    DevState h{};
     h.b = b;
     h.x = x;
     h.tol = tol;
@@ -513,7 +512,7 @@ sstep_status start_state(sstep_ctx *ctx, const double *b, double *x, double tol,
     h.max_outer = no_stop ? (1 << 30) : ctx->opt.max_outer;
     h.hist_cap = ctx->it.hist_cap;
     OKCHK(order_after_user(ctx));
-    HIPCHK(ctx, hipMemcpyAsync(ctx->it.st, &h, sizeof(DevState), hipMemcpyHostToDevice, ctx->stream));
+    HIPCHK(ctx, launch_init_state(ctx->it.st, h, ctx->stream));
     if (ctx->it.fp32) {
         HIPCHK(ctx, launch_residual(ctx->it, ctx->stream, false));
         HIPCHK(ctx, launch_p0scale(ctx->it, ctx->stream));
@@ -691,6 +690,12 @@ sstep_status capture_graph(sstep_ctx *ctx)
     return SSTEP_OK;
 }
 
+// Graph replays that hold the iterations 0 .. max_outer.
+int64_t replay_bound(const sstep_ctx *ctx)
+{
+    return (int64_t(ctx->opt.max_outer) + ctx->chunk) / ctx->chunk;
+}
+
 sstep_status run_solve(sstep_ctx *ctx, const double *b, double *x, double tol, sstep_stats *stats)
 {
     if (!ctx)
@@ -702,14 +707,15 @@ sstep_status run_solve(sstep_ctx *ctx, const double *b, double *x, double tol, s
     if (!(tol > 0.0) || !(tol < 1.0))
         return fail(ctx, SSTEP_E_ARG, "tol must be in (0, 1)");
     OKCHK(start_state(ctx, b, x, tol, 0));
-    const int max_replays = (ctx->opt.max_outer + 1 + ctx->chunk - 1) / ctx->chunk + 1;
-    int launched = 0, checked = 0;
+    // iterations 0 .. max_outer, the last of which only tests the residual
+    const int64_t max_replays = replay_bound(ctx);
+    int64_t launched = 0, checked = 0;
     auto enqueue = [&]() -> hipError_t {
         hipError_t e = hipGraphLaunch(ctx->gexec, ctx->stream);
         if (e != hipSuccess)
             return e;
-        int32_t *slot = ctx->poll_host + 4 * (launched % 2);
-        e = hipMemcpyAsync(slot, &ctx->it.st->done, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(&ctx->st_host[launched % 2], ctx->it.st, sizeof(DevState), hipMemcpyDeviceToHost,
+                           ctx->stream);
         if (e != hipSuccess)
             return e;
         e = hipEventRecord(ctx->ev_poll[launched % 2], ctx->stream);
@@ -717,22 +723,31 @@ sstep_status run_solve(sstep_ctx *ctx, const double *b, double *x, double tol, s
         return e;
     };
     HIPCHK(ctx, enqueue());
+    // One replay stays queued behind the one being waited for, so that the
+    // device does not wait for the host, unless the one in flight is expected
+    // to be the last: a replay after the stop still starts every kernel.  The
+    // expectation extrapolates the last two residuals read back.
+    bool last = false;
+    double relres = 1.0;
     for (;;) {
-        if (launched < max_replays)
-            HIPCHK(ctx, enqueue());  // keep one replay queued behind the one being checked
+        if (launched < max_replays && (!last || checked == launched))
+            HIPCHK(ctx, enqueue());
         HIPCHK(ctx, hipEventSynchronize(ctx->ev_poll[checked % 2]));
-        const int32_t done = ctx->poll_host[4 * (checked % 2)];
+        const DevState &h = ctx->st_host[checked % 2];
         ++checked;
-        if (done)
+        if (h.done)
             break;
-        if (checked >= launched) {
+        if (checked >= max_replays) {
             HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
             return fail(ctx, SSTEP_E_HIP, "solve did not stop within the replay bound");
         }
+        // relres belongs to the replay's last iteration; the next replay ends
+        // chunk iterations further
+        last = h.relres > 0.0 && h.relres < relres && h.relres * (h.relres / relres) < tol;
+        relres = h.relres;
     }
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    DevState h;
-    HIPCHK(ctx, hipMemcpy(&h, ctx->it.st, sizeof(DevState), hipMemcpyDeviceToHost));
+    const DevState h = ctx->st_host[(checked - 1) % 2];
     if (stats) {
         stats->outer_iters = h.iter;
         stats->status = h.status;
@@ -883,13 +898,12 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_poll[1], hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
-    OKCHK(order_after_user(ctx));
+    if (A->ptr_space)
+        OKCHK(order_after_user(ctx));
     {
         void *p = nullptr;
-        HIPCHK(ctx, hipHostMalloc(&p, sizeof(DevState), hipHostMallocDefault));
+        HIPCHK(ctx, hipHostMalloc(&p, 2 * sizeof(DevState), hipHostMallocDefault));
         ctx->st_host = static_cast<DevState *>(p);
-        HIPCHK(ctx, hipHostMalloc(&p, 8 * sizeof(int32_t), hipHostMallocDefault));
-        ctx->poll_host = static_cast<int32_t *>(p);
     }
 
     IterArgs &it = ctx->it;
@@ -1028,7 +1042,8 @@ sstep_status sstep_update_coefficients(sstep_ctx *ctx, const sstep_operator *A)
         if (op.kind == kOpPoisson || op.kind == kOpPoisson27)
             return SSTEP_OK;  // no coefficients
     }
-    OKCHK(order_after_user(ctx));
+    if (A->ptr_space)
+        OKCHK(order_after_user(ctx));
     return load_coefficients(ctx, A, false);
 }
 
@@ -1551,7 +1566,8 @@ static sstep_status setup_batched_impl(sstep_ctx *ctx, int32_t nsys, const sstep
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_poll[1], hipEventDisableTiming));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
-    OKCHK(order_after_user(ctx));
+    if (std::any_of(A, A + nsys, [](const sstep_operator &q) { return q.ptr_space != 0; }))
+        OKCHK(order_after_user(ctx));
     ctx->batch = new (std::nothrow) Batched();
     if (!ctx->batch)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");
@@ -1866,8 +1882,8 @@ sstep_status sstep_solve_batched(sstep_ctx *ctx, const double *const *b, double 
         HIPCHK(ctx, launch_bresidual(a, ctx->stream, false));
         HIPCHK(ctx, launch_bp0scale(a, ctx->stream));
     }
-    const int max_replays = (ctx->opt.max_outer + 1 + ctx->chunk - 1) / ctx->chunk + 1;
-    int launched = 0, checked = 0;
+    const int64_t max_replays = replay_bound(ctx);
+    int64_t launched = 0, checked = 0;
     // the short-range graph once the blocks the whole batch's band table
     // would still start (as of the last replay read back) fall below
     // kBf2BlocksPerCu per CU; the choice depends only on device results, so
@@ -1902,13 +1918,14 @@ sstep_status sstep_solve_batched(sstep_ctx *ctx, const double *const *b, double 
         ++checked;
         if (ndone >= a.npairs)
             break;
-        if (checked >= launched) {
+        if (checked >= max_replays) {
             HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
             return fail(ctx, SSTEP_E_HIP, "batched solve did not stop within the replay bound");
         }
     }
+    HIPCHK(ctx, hipMemcpyAsync(B.pairs_host, a.pairs, sizeof(DevState) * size_t(a.npairs), hipMemcpyDeviceToHost,
+                               ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-    HIPCHK(ctx, hipMemcpy(B.pairs_host, a.pairs, sizeof(DevState) * size_t(a.npairs), hipMemcpyDeviceToHost));
     sstep_status first_bad = SSTEP_OK;
     for (int p = 0; p < a.npairs; ++p) {
         const DevState &h = B.pairs_host[p];
@@ -1948,7 +1965,8 @@ static sstep_status coarse_setup_impl(sstep_ctx *ctx, const sstep_operator *Af, 
     HIPCHK(ctx, hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking));
     ctx->user = static_cast<hipStream_t>(ctx->opt.stream);
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming));
-    OKCHK(order_after_user(ctx));
+    if (Af->ptr_space)
+        OKCHK(order_after_user(ctx));
     ctx->coarse = new (std::nothrow) CoarseArgs();
     if (!ctx->coarse)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");
@@ -2244,12 +2262,19 @@ sstep_status noalloc_impl(const sstep_operator *A, int32_t s, int32_t nu, double
         if (hbad)
             return fail(nullptr, SSTEP_E_ARG, "matrix has a missing, non-positive or non-finite diagonal entry");
     }
-    HIPCHK(nullptr, launch_init_state(it.st, b, x, tol, o.max_outer, st));
+    DevState init{};
+    init.b = b;
+    init.x = x;
+    init.tol = tol;
+    init.p0scale = 1.0;
+    init.first = 1;
+    init.max_outer = o.max_outer;
+    HIPCHK(nullptr, launch_init_state(it.st, init, st));
 
     // outer iterations in chunks of graph_chunk launches, then a look at the
     // device's stop flag (every kernel returns at once after the stop)
     const int chunk = o.graph_chunk > 0 ? o.graph_chunk : 4;
-    const int64_t max_chunks = (int64_t(o.max_outer) + 1 + chunk - 1) / chunk + 1;
+    const int64_t max_chunks = (int64_t(o.max_outer) + chunk) / chunk;
     int32_t done = 0;
     for (int64_t c = 0; c < max_chunks && !done; ++c) {
         for (int q = 0; q < chunk; ++q)

@@ -894,18 +894,10 @@ __global__ __launch_bounds__(kBlock) void k_fill_zero(uint64_t *__restrict__ p, 
         p[q] = 0;
 }
 
-__global__ void k_init_state(DevState *__restrict__ s, const double *b, double *x, double tol, int max_outer)
+__global__ void k_init_state(DevState *__restrict__ s, DevState h)
 {
-    if (threadIdx.x != 0)
-        return;
-    DevState h{};
-    h.b = b;
-    h.x = x;
-    h.tol = tol;
-    h.p0scale = 1.0;
-    h.first = 1;
-    h.max_outer = max_outer;
-    *s = h;
+    if (threadIdx.x == 0)
+        *s = h;
 }
 
 // Row pointers of a CSR pattern: rp[0] = 0, rp[n] = nnz, non-decreasing.
@@ -986,9 +978,9 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_init_state(DevState *s, const double *b, double *x, double tol, int max_outer, hipStream_t st)
+hipError_t launch_init_state(DevState *s, const DevState &h, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(kWave), 0, st, s, b, x, tol, max_outer);
+    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(kWave), 0, st, s, h);
     return hipGetLastError();
 }
 
