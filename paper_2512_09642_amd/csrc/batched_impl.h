@@ -184,14 +184,13 @@ __device__ __forceinline__ void bfgs_map_sweep(BGlob *__restrict__ gl, DevState 
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const double theta = Q.theta, sigma = Q.sigma;
     auto H = [&](int a, int b) { return a >= b ? h[tri_index(a, b)] : h[tri_index(b, a)]; };
-    for (int e = threadIdx.x; e < T0; e += kBFgsThreads) {
-        int i = 0;
-        while ((i + 1) * (i + 2) / 2 <= e)
-            ++i;
-        const int j = e - i * (i + 1) / 2;
+    for (int e = threadIdx.x; e < S * S; e += kBFgsThreads) {
+        const int i = e / S, j = e % S;
+        if (j > i)
+            continue;
         const double g = j == 0 ? H(i, 1) / theta + sigma * H(i, 0)
                                 : (H(i, j + 1) + H(i, j - 1)) / (2.0 * theta) + sigma * H(i, j);
-        sg[e] = hscale * g;
+        sg[tri_index(i, j)] = hscale * g;
     }
     for (int i = threadIdx.x; i < S; i += kBFgsThreads)
         sg[T0 + i] = h[S1 * (S1 + 1) / 2 + i];
@@ -325,12 +324,10 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_mom(BGlob *__restrict__ g
     for (int k = threadIdx.x; k < NS; k += kBFgsThreads)
         mu[k] = k <= 1 ? m[k] : 2.0 * m[k] - m[k % 2];
     __syncthreads();
-    for (int e = threadIdx.x; e < S1 * (S1 + 1) / 2; e += kBFgsThreads) {
-        int i = 0;
-        while ((i + 1) * (i + 2) / 2 <= e)
-            ++i;
-        const int j = e - i * (i + 1) / 2;
-        h[e] = 0.5 * (mu[i + j] + mu[i - j]);
+    for (int e = threadIdx.x; e < S1 * S1; e += kBFgsThreads) {
+        const int i = e / S1, j = e % S1;
+        if (j <= i)
+            h[tri_index(i, j)] = 0.5 * (mu[i + j] + mu[i - j]);
     }
     for (int i = threadIdx.x; i < S1; i += kBFgsThreads)
         h[S1 * (S1 + 1) / 2 + i] = mu[i];

@@ -76,14 +76,71 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t per)
     return (b % kNumXcd) * per + b / kNumXcd;
 }
 
-// Butterfly sum over the 64 lanes of a wave; every lane gets the total and the
-// order of the additions is fixed, so the result is reproducible.
+// A 32-bit register moved between lanes on the vector ALU.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;        // quad_perm 1,0,3,2 / 2,3,0,1
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;      // rotations within a row of 16 lanes
+constexpr int kDppRowNewBcast = 0x150;                 // + l: lane l of each row to its whole row
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v)
+{
+    return __hiloint2double(static_cast<int>(dpp_mov<CTRL>(static_cast<uint32_t>(__double2hiint(v)))),
+                            static_cast<int>(dpp_mov<CTRL>(static_cast<uint32_t>(__double2loint(v)))));
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __uint_as_float(dpp_mov<CTRL>(__float_as_uint(v)));
+}
+
+// v + its value ROWS / 16 rows of 16 lanes away (ROWS 32: the other half of
+// the wave; 16: the other row of the half), in every lane.
+template <int ROWS>
+__device__ __forceinline__ void swap_rows(uint32_t &a, uint32_t &b)
+{
+    static_assert(ROWS == 16 || ROWS == 32, "rows exchanged by one instruction");
+    const auto r = ROWS == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                              : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0], b = r[1];
+}
+template <int ROWS>
+__device__ __forceinline__ double add_rows(double v)
+{
+    uint32_t l0 = static_cast<uint32_t>(__double2loint(v)), l1 = l0;
+    uint32_t h0 = static_cast<uint32_t>(__double2hiint(v)), h1 = h0;
+    swap_rows<ROWS>(l0, l1);
+    swap_rows<ROWS>(h0, h1);
+    return __hiloint2double(static_cast<int>(h0), static_cast<int>(l0)) +
+           __hiloint2double(static_cast<int>(h1), static_cast<int>(l1));
+}
+template <int ROWS>
+__device__ __forceinline__ float add_rows(float v)
+{
+    uint32_t a = __float_as_uint(v), b = a;
+    swap_rows<ROWS>(a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+
+// Butterfly sum over the 64 lanes of a wave (lanes 32 apart, then 16, 8, 4, 2,
+// 1); every lane gets the total and the order of the additions is fixed, so
+// the result is reproducible.  Formed by lane moves on the vector ALU: the
+// same six exchanges through the LDS permute unit take some 600 cycles, which
+// a kernel of a few microseconds shows at its end.  (After the step over 8
+// lanes a row repeats itself, so a rotation by 4 meets the lane 4 apart.)
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1)
-        v += __shfl_xor(v, off, kWave);
+    v = add_rows<32>(v);
+    v = add_rows<16>(v);
+    v += dpp<kDppRor8>(v);
+    v += dpp<kDppRor4>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppXor1>(v);
     return v;
 }
 

@@ -16,6 +16,26 @@ __device__ __forceinline__ double readlane(double v, int l)
     return __hiloint2double(hi, lo);
 }
 
+// The updates j .. s - 1 of one sweep of fgs_wave.
+template <int s, int j>
+struct Sweep {
+    static __device__ __forceinline__ void run(double &rv, double &a, const double (&grow)[s], int lane)
+    {
+        double delta;
+        if constexpr (s <= 16)
+            delta = dpp<kDppRowNewBcast + j % 16>(rv);
+        else
+            delta = readlane(rv, j);
+        a = __builtin_fma(lane == j ? 1.0 : 0.0, rv, a);
+        rv -= grow[j] * delta;
+        Sweep<s, j + 1>::run(rv, a, grow, lane);
+    }
+};
+template <int s>
+struct Sweep<s, s> {
+    static __device__ __forceinline__ void run(double &, double &, const double (&)[s], int) {}
+};
+
 // sg holds the reduced sums: Gram entries in canonical order (lower triangle
 // row by row, then the right-hand side).  The stopping test of iteration k
 // has already run (stop.h), and st->rho holds ||r_k||.
@@ -79,16 +99,13 @@ __device__ __forceinline__ int fgs_wave(DevState *__restrict__ st, const double 
     }
 
     // ---- forward Gauss-Seidel, residual form ---------------------------------
+    // A chain of nu s dependent updates, one wave: the value a step needs from
+    // lane j comes by a DPP broadcast within the row of 16 lanes (s <= 16:
+    // rows 1..3 hold zeros), else by readlane; atil_j gathers its steps with a
+    // 0/1 factor, beside the chain (atil_i + 0 adds nothing).
     double rv = ct, a = 0.0;
-    for (int sweep = 0; sweep < nu; ++sweep) {
-#pragma unroll
-        for (int j = 0; j < s; ++j) {
-            const double delta = readlane(rv, j);
-            if (i == j)
-                a += delta;
-            rv -= grow[j] * delta;
-        }
-    }
+    for (int sweep = 0; sweep < nu; ++sweep)
+        Sweep<s, 0>::run(rv, a, grow, i);
 
     // ---- outputs --------------------------------------------------------------
     double res = ct;
@@ -104,8 +121,9 @@ __device__ __forceinline__ int fgs_wave(DevState *__restrict__ st, const double 
         if (j < i)
             lsq += grow[j] * grow[j];
     const double lnorm = sqrt(wave_sum(lsq));
-    if (own) {
+    if (own)
         st->alpha[i] = d * a;
+    if (own && st->no_stop) {  // read back by the single-step entry point only
         dbg[dbg_ctil(s) + i] = ct;
         dbg[dbg_atil(s) + i] = a;
         dbg[dbg_d(s) + i] = d;
@@ -205,11 +223,10 @@ __device__ __forceinline__ void fgs_rec_from_h(DevState *__restrict__ st, const 
     constexpr int T0 = s * (s + 1) / 2;
     __shared__ double sg[T0 + s];
     auto H = [&](int a, int b) { return a >= b ? h[tri_index(a, b)] : h[tri_index(b, a)]; };
-    for (int e = threadIdx.x; e < T0; e += kFgsThreads) {
-        int i = 0;
-        while ((i + 1) * (i + 2) / 2 <= e)
-            ++i;
-        const int j = e - i * (i + 1) / 2;
+    for (int e = threadIdx.x; e < s * s; e += kFgsThreads) {
+        const int i = e / s, j = e % s;
+        if (j > i)
+            continue;
         double g;
         if (monomial)
             g = H(i, j + 1);
@@ -217,7 +234,7 @@ __device__ __forceinline__ void fgs_rec_from_h(DevState *__restrict__ st, const 
             g = H(i, 1) / theta + sigma * H(i, 0);
         else
             g = (H(i, j + 1) + H(i, j - 1)) / (2.0 * theta) + sigma * H(i, j);
-        sg[e] = hscale * g;
+        sg[tri_index(i, j)] = hscale * g;
     }
     for (int i = threadIdx.x; i < s; i += kFgsThreads)
         sg[T0 + i] = h[S1 * (S1 + 1) / 2 + i];
@@ -278,12 +295,10 @@ __global__ __launch_bounds__(kFgsThreads) void k_fgs_mom(DevState *__restrict__ 
         mu[k] = m;
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < S1 * (S1 + 1) / 2; e += kFgsThreads) {
-        int i = 0;
-        while ((i + 1) * (i + 2) / 2 <= e)
-            ++i;
-        const int j = e - i * (i + 1) / 2;
-        h[e] = 0.5 * (mu[i + j] + mu[i - j]);
+    for (int e = threadIdx.x; e < S1 * S1; e += kFgsThreads) {
+        const int i = e / S1, j = e % S1;
+        if (j <= i)
+            h[tri_index(i, j)] = 0.5 * (mu[i + j] + mu[i - j]);
     }
     for (int i = threadIdx.x; i < S1; i += kFgsThreads)
         h[S1 * (S1 + 1) / 2 + i] = mu[i];

@@ -152,32 +152,15 @@ __global__ __launch_bounds__(kBlock) void k_coarse_zero(double *__restrict__ a, 
 
 constexpr int kHalf = kWave / 2;  // lanes per unknown
 
-// v plus the value of the lane that a DPP control selects.
-template <int CTRL>
-__device__ __forceinline__ double add_dpp(double v)
-{
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
-    return v + __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double lane_value(double v, int l)
-{
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
-                            __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-
 // Sum over the 32 lanes of a half wave, in a fixed order; every lane gets it.
-// Within a row of 16 lanes by DPP (neighbours, pairs, the mirrored half row,
-// the mirrored row), then the two rows of the half.
 __device__ __forceinline__ double half_sum(double v)
 {
-    v = add_dpp<0xB1>(v);   // quad_perm 1,0,3,2
-    v = add_dpp<0x4E>(v);   // quad_perm 2,3,0,1
-    v = add_dpp<0x141>(v);  // row_half_mirror
-    v = add_dpp<0x140>(v);  // row_mirror
-    const double a = lane_value(v, 0) + lane_value(v, 16), b = lane_value(v, 32) + lane_value(v, 48);
-    return threadIdx.x % kWave < kHalf ? a : b;
+    v = add_rows<16>(v);
+    v += dpp<kDppRor8>(v);
+    v += dpp<kDppRor4>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppXor1>(v);
+    return v;
 }
 
 // One update of unknown j by half a wave, streamed: lane l < 27 owns fine
