@@ -25,6 +25,8 @@ ARCH = "gfx950"
 
 CFLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall", "-Wno-unused-result",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+          # leading kernel arguments arrive in registers instead of by a load (launch-bound solves: 2-5% faster)
+          "-mllvm", "-amdgpu-kernarg-preload-count=16",
           "-I", INCLUDE, "-I", CSRC]
 
 

@@ -973,6 +973,7 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
     if (it.gram_mom) {
         std::vector<int32_t> cnt(size_t(2 * s + 1), 0);
         mom_layout(it, cnt.data(), &it.mstride);
+        it.small = small_chain(it);
         OKCHK(dalloc(ctx, &it.mpart, size_t(2 * s + 1) * size_t(it.mstride)));
         OKCHK(dalloc(ctx, &it.mcnt, cnt.size()));
         HIPCHK(ctx, hipMemcpy(it.mcnt, cnt.data(), cnt.size() * sizeof(int32_t), hipMemcpyHostToDevice));

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kFgsThreads) void k_fgs(DevState *__restrict__ st, 
 // block writes G_raw (lower triangle) and c' for the s columns into LDS in
 // the layout of k_fgs, then wave 0 runs fgs_wave.
 // The block's part after h (LDS, the layout above) is filled and synchronised.
-template <int s>
+template <int s, int NT>
 __device__ __forceinline__ void fgs_rec_from_h(DevState *__restrict__ st, const double *h, int nu, double cscale,
                                                int fp32, double inv_sqrt_n, double *__restrict__ dbg,
                                                double *__restrict__ hist, int hist_cap, double theta, double sigma,
@@ -223,7 +223,7 @@ __device__ __forceinline__ void fgs_rec_from_h(DevState *__restrict__ st, const 
     constexpr int T0 = s * (s + 1) / 2;
     __shared__ double sg[T0 + s];
     auto H = [&](int a, int b) { return a >= b ? h[tri_index(a, b)] : h[tri_index(b, a)]; };
-    for (int e = threadIdx.x; e < s * s; e += kFgsThreads) {
+    for (int e = threadIdx.x; e < s * s; e += NT) {
         const int i = e / s, j = e % s;
         if (j > i)
             continue;
@@ -236,7 +236,7 @@ __device__ __forceinline__ void fgs_rec_from_h(DevState *__restrict__ st, const 
             g = (H(i, j + 1) + H(i, j - 1)) / (2.0 * theta) + sigma * H(i, j);
         sg[tri_index(i, j)] = hscale * g;
     }
-    for (int i = threadIdx.x; i < s; i += kFgsThreads)
+    for (int i = threadIdx.x; i < s; i += NT)
         sg[T0 + i] = h[S1 * (S1 + 1) / 2 + i];
     __syncthreads();
     if (threadIdx.x / kWave != 0)
@@ -259,7 +259,8 @@ __global__ __launch_bounds__(kFgsThreads) void k_fgs_rec(DevState *__restrict__ 
     for (int t = threadIdx.x; t < E1; t += kFgsThreads)
         h[t] = sums[t];
     __syncthreads();
-    fgs_rec_from_h<s>(st, h, nu, cscale, fp32, inv_sqrt_n, dbg, hist, hist_cap, theta, sigma, hscale, monomial);
+    fgs_rec_from_h<s, kFgsThreads>(st, h, nu, cscale, fp32, inv_sqrt_n, dbg, hist, hist_cap, theta, sigma, hscale,
+                                   monomial);
 }
 
 // The Gram matrix of the Chebyshev basis from its moments.  With
@@ -272,38 +273,71 @@ __global__ __launch_bounds__(kFgsThreads) void k_fgs_rec(DevState *__restrict__ 
 // so the 2s + 1 products d_i, e_i fix all of H (p_0 .. p_s), and the
 // right-hand side c'_i = <p_i, M p_0> = mu_i.  The block forms h in the
 // recurrence kind's layout and continues as k_fgs_rec.
-template <int s>
-__global__ __launch_bounds__(kFgsThreads) void k_fgs_mom(DevState *__restrict__ st, const double *__restrict__ sums,
-                                                         int nu, double cscale, int fp32, double inv_sqrt_n,
-                                                         double *__restrict__ dbg, double *__restrict__ hist,
-                                                         int hist_cap, double theta, double sigma, double hscale)
+// SUM (small_chain): sums holds the block partials of the products, nb of each,
+// and the block sums them in the order of k_mom_sums, a quarter of its threads
+// a product at a time; else sums holds the products.
+constexpr int kFgsSumThreads = 1024;
+template <int s, bool SUM>
+__global__ __launch_bounds__(SUM ? kFgsSumThreads : kFgsThreads) void k_fgs_mom(
+    DevState *__restrict__ st, const double *__restrict__ sums, int nb, int nu, double cscale, int fp32,
+    double inv_sqrt_n, double *__restrict__ dbg, double *__restrict__ hist, int hist_cap, double theta, double sigma,
+    double hscale)
 {
-    if (st->done)
-        return;
+    constexpr int NT = SUM ? kFgsSumThreads : kFgsThreads;
     constexpr int S1 = s + 1;
     constexpr int E1 = S1 * (S1 + 1) / 2 + S1;
+    __shared__ double prod[2 * s + 1];
     __shared__ double mu[2 * s + 1];
     __shared__ double h[E1];
-    for (int k = threadIdx.x; k <= 2 * s; k += kFgsThreads) {
-        double m;
-        if (k <= 1)
-            m = sums[k];
-        else if (k % 2 == 0)
-            m = 2.0 * sums[k] - sums[0];
-        else
-            m = 2.0 * sums[k] - sums[1];
-        mu[k] = m;
+    const int done = st->done;
+    if constexpr (SUM) {
+        constexpr int G = NT / kSumThreads, WG = kSumThreads / kWave;  // products at a time, waves of each
+        __shared__ double part[2 * s + 1][WG];
+        const int g = threadIdx.x / kSumThreads, t = threadIdx.x % kSumThreads;
+        constexpr int NP = (2 * s + G) / G;  // products of a quarter: g, g + G, ...
+        double acc[NP];
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            acc[u] = 0.0;
+        for (int q = t; q < nb; q += kSumThreads)
+#pragma unroll
+            for (int u = 0; u < NP; ++u)
+                if (g + u * G <= 2 * s)
+                    acc[u] += sums[static_cast<int64_t>(g + u * G) * nb + q];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const double v = wave_sum(acc[u]);
+            if (g + u * G <= 2 * s && t % kWave == 0)
+                part[g + u * G][t / kWave] = v;
+        }
+        if (done)
+            return;
+        __syncthreads();
+        if (threadIdx.x <= 2 * s) {
+            double v = 0.0;
+            for (int w = 0; w < WG; ++w)
+                v += part[threadIdx.x][w];
+            prod[threadIdx.x] = v;
+        }
+    } else {
+        if (done)
+            return;
+        for (int k = threadIdx.x; k <= 2 * s; k += NT)
+            prod[k] = sums[k];
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < S1 * S1; e += kFgsThreads) {
+    for (int k = threadIdx.x; k <= 2 * s; k += NT)
+        mu[k] = k <= 1 ? prod[k] : 2.0 * prod[k] - prod[k % 2];
+    __syncthreads();
+    for (int e = threadIdx.x; e < S1 * S1; e += NT) {
         const int i = e / S1, j = e % S1;
         if (j <= i)
             h[tri_index(i, j)] = 0.5 * (mu[i + j] + mu[i - j]);
     }
-    for (int i = threadIdx.x; i < S1; i += kFgsThreads)
+    for (int i = threadIdx.x; i < S1; i += NT)
         h[S1 * (S1 + 1) / 2 + i] = mu[i];
     __syncthreads();
-    fgs_rec_from_h<s>(st, h, nu, cscale, fp32, inv_sqrt_n, dbg, hist, hist_cap, theta, sigma, hscale, 0);
+    fgs_rec_from_h<s, NT>(st, h, nu, cscale, fp32, inv_sqrt_n, dbg, hist, hist_cap, theta, sigma, hscale, 0);
 }
 
 template <int s>
@@ -320,8 +354,13 @@ hipError_t fgs_rec_launch_s(const IterArgs &a, hipStream_t st)
 template <int s>
 hipError_t fgs_mom_launch_s(const IterArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fgs_mom<s>, dim3(1), dim3(kFgsThreads), 0, st, a.st, a.gsum, a.nu, a.cscale, a.fp32,
-                       a.inv_sqrt_n, a.dbg, a.hist, a.hist_cap, a.theta, a.sigma, a.rec_hscale);
+    if (a.small)
+        hipLaunchKernelGGL((k_fgs_mom<s, true>), dim3(1), dim3(kFgsSumThreads), 0, st, a.st, a.mpart,
+                           static_cast<int>(a.mstride), a.nu, a.cscale, a.fp32, a.inv_sqrt_n, a.dbg, a.hist,
+                           a.hist_cap, a.theta, a.sigma, a.rec_hscale);
+    else
+        hipLaunchKernelGGL((k_fgs_mom<s, false>), dim3(1), dim3(kFgsThreads), 0, st, a.st, a.gsum, 0, a.nu, a.cscale,
+                           a.fp32, a.inv_sqrt_n, a.dbg, a.hist, a.hist_cap, a.theta, a.sigma, a.rec_hscale);
     return hipGetLastError();
 }
 

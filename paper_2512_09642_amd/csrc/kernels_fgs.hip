@@ -57,7 +57,7 @@ hipError_t launch_mom_sums(const IterArgs &a, hipStream_t st)
 hipError_t launch_gram(const IterArgs &a, hipStream_t st)
 {
     if (a.gram_mom)  // the basis kernels formed the products: only their sums remain
-        return launch_mom_sums(a, st);
+        return a.small ? hipSuccess : launch_mom_sums(a, st);
     if (a.gram_rec) {
 #define SSTEP_GS(S)                                                                          \
     case S:                                                                                  \

@@ -26,6 +26,15 @@ inline uint32_t blocks_for(int64_t n) { return static_cast<uint32_t>((n + kBlock
 // -> 8.9 us, 7-point CSR 16^3 3.9 -> 3.5; equal from 40^3 on, where the
 // residual's 1024 blocks of one wave are slower (5.8 -> 7.4 us).
 constexpr int64_t kWaveBlocksMax = 32768;
+// Unknowns up to which an outer iteration is taken for a chain of launches
+// (small_chain): there two launches fewer, of 2 to 3 us each, are worth more
+// than what they add to the two that take over their work, every block of the
+// first basis launch summing the residual's partials (at most 1024) and the
+// Gram solve's one block 2s + 1 rows of at most 512.  A solve of
+// CSR 64x64, s = 8: 5 % of 1.1 ms; of 7-point 45^3, s = 16: 1 % of 7.3 ms.
+// Beyond, the partials of the residual's marched blocks and of the pairs come
+// in other counts, and the two launches are below 2 % of an iteration.
+constexpr int64_t kSmallMax = 131072;
 inline int point_threads(int64_t n) { return n <= kWaveBlocksMax ? kWave : kBlock; }
 
 Launch1D plan_points(int64_t n, int threads = kBlock)
@@ -137,12 +146,13 @@ __global__ __launch_bounds__(NT) void k_basis(const DevState *__restrict__ st, O
 // first when j = 0, written to consecutive slots of mpart (stride mstride),
 // one value per logical block.  The threads past n take part in the block
 // sums with weight 0.
-template <class Op, typename T, int STEP, int NT>
-__global__ __launch_bounds__(NT) void k_basis_mom(const DevState *__restrict__ st, Op op,
-                                                      const T *__restrict__ pj, const T *__restrict__ pprev,
-                                                      T *__restrict__ pnext, T theta, T sigma, int64_t n,
-                                                      uint32_t per, uint32_t nbl, double *__restrict__ mpart,
-                                                      int64_t mstride)
+// STOP (small_chain, j = 0): the launch also makes the stopping test.
+template <class Op, typename T, int STEP, int NT, bool STOP>
+__global__ __launch_bounds__(NT) void k_basis_mom(DevState *__restrict__ st, const T *__restrict__ pj,
+                                                      const T *__restrict__ pprev, T *__restrict__ pnext, T theta,
+                                                      T sigma, int64_t n, uint32_t per, uint32_t nbl,
+                                                      double *__restrict__ mpart, int64_t mstride, StopArgs stop,
+                                                      Op op)
 {
     static_assert(STEP == 0 || STEP == 1, "the moments kind forms every column");
     if (st->done)
@@ -150,6 +160,9 @@ __global__ __launch_bounds__(NT) void k_basis_mom(const DevState *__restrict__ s
     const uint32_t lb = xcd_block(blockIdx.x, per);
     if (lb >= nbl)
         return;  // whole block
+    double share = 0.0;
+    if constexpr (STOP)
+        share = partial_share<NT>(stop);
     const int64_t c = static_cast<int64_t>(lb) * NT + threadIdx.x;
     const bool valid = c < n;
     const int64_t cc = valid ? c : n - 1;
@@ -160,6 +173,9 @@ __global__ __launch_bounds__(NT) void k_basis_mom(const DevState *__restrict__ s
         pn = theta * (dinv * y - sigma * pc);
     else
         pn = T(2) * theta * (dinv * y - sigma * pc) - __builtin_nontemporal_load(pprev + cc);
+    if constexpr (STOP)
+        if (stop_at_head<NT>(st, stop, share, lb == 0))
+            return;
     if (valid)
         pnext[c] = pn;
     const double w = valid ? static_cast<double>(wt) : 0.0;
@@ -618,12 +634,16 @@ hipError_t basis_for_nt(const IterArgs &a, const Op &op, int j, int step, hipStr
         if (step == 2)
             return hipErrorInvalidValue;
         double *mp = a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride;
-        if (step == 0)
-            hipLaunchKernelGGL((k_basis_mom<Op, T, 0, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev,
-                               pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride);
+        const StopArgs stop{a.rpart, a.dbg + dbg_rho(a.s), a.hist, a.nbr, a.hist_cap};
+        if (a.small && step == 0)
+            hipLaunchKernelGGL((k_basis_mom<Op, T, 0, NT, true>), dim3(l.grid), dim3(NT), 0, st, a.st, pj, pprev,
+                               pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride, stop, op);
+        else if (step == 0)
+            hipLaunchKernelGGL((k_basis_mom<Op, T, 0, NT, false>), dim3(l.grid), dim3(NT), 0, st, a.st, pj, pprev,
+                               pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride, stop, op);
         else
-            hipLaunchKernelGGL((k_basis_mom<Op, T, 1, NT>), dim3(l.grid), dim3(NT), 0, st, a.st, op, pj, pprev,
-                               pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride);
+            hipLaunchKernelGGL((k_basis_mom<Op, T, 1, NT, false>), dim3(l.grid), dim3(NT), 0, st, a.st, pj, pprev,
+                               pnext, theta, sigma, a.op.n, l.per, l.nbl, mp, a.mstride, stop, op);
         return hipGetLastError();
     }
     if (step == 2)
@@ -1008,8 +1028,8 @@ int residual_march_blocks(const OpDev &op)
 hipError_t launch_residual(const IterArgs &a, hipStream_t st, bool write_p0)
 {
     const hipError_t e = a.fp32 ? residual_t<float>(a, st, write_p0) : residual_t<double>(a, st, write_p0);
-    if (e != hipSuccess || !write_p0)
-        return e;  // the norm-only pass of FP32+IR runs no stopping test
+    if (e != hipSuccess || !write_p0 || a.small)
+        return e;  // the norm-only pass of FP32+IR runs no stopping test; a small system's first basis launch does
     hipLaunchKernelGGL(k_stop, dim3(1), dim3(kSumThreads), 0, st, a.st, a.rpart, a.nbr, a.dbg + dbg_rho(a.s), a.hist,
                        a.hist_cap);
     return hipGetLastError();
@@ -1048,6 +1068,11 @@ int basis_kernel_count(const IterArgs &a, int *pairs)
     if (pairs)
         *pairs = m / 2;
     return m / 2 + m % 2;
+}
+
+bool small_chain(const IterArgs &a)
+{
+    return a.gram_mom && a.op.n <= kSmallMax && !basis_pairs_apply(a) && !march_step(a.op, 8);
 }
 
 hipError_t launch_basis_all(const IterArgs &a, hipStream_t st)

@@ -103,6 +103,9 @@ struct IterArgs {
     double *mpart = nullptr;
     int32_t *mcnt = nullptr;
     int64_t mstride = 0;
+    // small systems (small_chain): the first basis launch makes the stopping
+    // test, the FGS kernel sums the products
+    int small = 0;
 };
 
 // Debug block layout written by the FGS kernel.
@@ -285,6 +288,9 @@ hipError_t launch_mom_sums(const IterArgs &a, hipStream_t st);
 // Launches launch_basis_all makes, and (if pairs is not NULL) how many of
 // them form two columns.
 int basis_kernel_count(const IterArgs &a, int *pairs);
+// Whether an outer iteration is so short that its launches are what it costs
+// (moments kind, a thread per point in every basis launch).
+bool small_chain(const IterArgs &a);
 // AP[:, j] = A p_j alone (into a.AP, which must be set).
 hipError_t launch_product(const IterArgs &a, int j, hipStream_t st);
 hipError_t launch_gram(const IterArgs &a, hipStream_t st);
