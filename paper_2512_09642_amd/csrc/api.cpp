@@ -991,7 +991,7 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
         l.n = n;
         l.nb = int(std::min<int64_t>(1024, (n + kBlock - 1) / kBlock));
         l.chunk = round_up((n + l.nb - 1) / l.nb, kBlock);
-        OKCHK(dalloc(ctx, &l.part, size_t(l.nb)));
+        OKCHK(dalloc(ctx, &l.part, size_t(2 * l.nb)));
         OKCHK(dalloc(ctx, &l.ab, size_t(3 * kMaxLanczos)));
         OKCHK(dalloc(ctx, &l.ls, 1));
     }

@@ -11,11 +11,16 @@
 // stopping early (m = j + 1 steps) when beta_{j+1} is not above
 // 1e-13 max_{i<=j} |alpha_i| or not finite.  The Ritz values are the
 // eigenvalues of the m x m tridiagonal T_m = tridiag(beta; alpha; beta),
-// found on the device by bisection on Sturm counts, one lane per eigenvalue.
+// found on the device by sections on Sturm counts, one wave per eigenvalue.
 //
-// Every pass is a streaming kernel over row chunks (one partial sum per
-// block, kSumThreads-thread fixed-order sums), HBM-bound like the basis
-// kernels; the whole estimate is a setup cost of a few passes per step.
+// A step is two passes over row chunks, HBM- (or cache-) bound like the basis
+// kernels, with one partial sum per block: the product and alpha, then w and
+// beta.  No launch of its own sums the partials or divides by beta: every
+// block of the next pass sums them in the same order (at most 1024, 8 KB from
+// the L2), and the vectors stay w, their divisors applied where they are read.
+// 10 steps on a 128^3 faces operator, s = 16: 571 -> 447 us per call; the
+// product 19.7 us and w 16.0 us at 5.1 and 5.3 TB/s out of the last-level
+// cache (twice the blocks: 20.1 and 19.0), the Ritz values 43 -> 13.6 us.
 #include "launch.h"
 #include "opsel.h"
 #include "stop.h"
@@ -59,9 +64,8 @@ __device__ __forceinline__ void block_partial(double v, double *out)
 }
 
 // Partial sums of ||u||_M^2 = sum d u^2.
-__global__ __launch_bounds__(kBlock) void k_lz_norm0(const LzState *__restrict__ ls, Diag dg,
-                                                     const double *__restrict__ u, double *__restrict__ part,
-                                                     int64_t n, int64_t chunk)
+__global__ __launch_bounds__(kBlock) void k_lz_norm0(Diag dg, const double *__restrict__ u,
+                                                     double *__restrict__ part, int64_t n, int64_t chunk)
 {
     const int64_t beg = static_cast<int64_t>(blockIdx.x) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
@@ -74,95 +78,112 @@ __global__ __launch_bounds__(kBlock) void k_lz_norm0(const LzState *__restrict__
     block_partial(acc, part + blockIdx.x);
 }
 
-// z = v / ls->scale (the start vector, or w with scale = beta_{j+1}).
-__global__ __launch_bounds__(kBlock) void k_lz_scale(const LzState *__restrict__ ls, const double *__restrict__ v,
-                                                     double *__restrict__ z, int64_t n)
+// Sum of the block partials by a block of kBlock threads, the same in every block
+// and in every thread.
+__device__ __forceinline__ double sum_partials(const double *__restrict__ part, int cnt)
 {
-    if (ls->stopped)
-        return;
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (c < n)
-        z[c] = v[c] / ls->scale;
+    double v = 0.0;
+    for (int q = threadIdx.x; q < cnt; q += kBlock)
+        v += part[q];
+    v = wave_sum(v);
+    __shared__ double wsum[kBlock / kWave];
+    if (threadIdx.x % kWave == 0)
+        wsum[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = wsum[0];
+#pragma unroll
+    for (int q = 1; q < kBlock / kWave; ++q)
+        v += wsum[q];
+    return v;
 }
 
-// y = A z_j and partial sums of z_j^T y.
-template <class Op>
-__global__ __launch_bounds__(kBlock) void k_lz_apply(const LzState *__restrict__ ls, Op op,
-                                                     const double *__restrict__ z, double *__restrict__ y,
-                                                     double *__restrict__ part, int64_t n, int64_t chunk)
+// beta_{j} ends the recurrence: not above 1e-13 amax, or not finite.
+__device__ __forceinline__ bool beta_stops(double beta, double amax)
 {
-    if (ls->stopped)
+    return !(beta > 1e-13 * amax) || !isfinite(beta);
+}
+
+// y = A z_j with z_j = w_j / scale, and partial sums of z_j^T y.  scale is
+// the root of the last partials: ||u||_M (j = 0, w_0 = u) or beta_j; the
+// first block records it and the end of the recurrence.
+template <class Op>
+__global__ __launch_bounds__(kBlock) void k_lz_apply(LzState *__restrict__ ls, const double *__restrict__ w,
+                                                     double *__restrict__ y, const double *__restrict__ pin,
+                                                     double *__restrict__ pout, double *__restrict__ ab, int j,
+                                                     int steps, int cnt, uint32_t per, int64_t n, int64_t chunk,
+                                                     Op op)
+{
+    const uint32_t lb = xcd_block(blockIdx.x, per);
+    if (ls->stopped || lb >= static_cast<uint32_t>(cnt))
+        return;  // whole block
+    const double scale = sqrt(sum_partials(pin, cnt));
+    // j = 0: amax = 0, a zero or non-finite start
+    const bool stop = beta_stops(scale, ls->amax);
+    if (lb == 0 && threadIdx.x == 0) {
+        if (j == 0)
+            ls->scale = scale;
+        else
+            ab[steps + j - 1] = scale;
+        ls->m = j;
+        if (stop)
+            ls->stopped = 1;
+    }
+    if (stop)
         return;
-    const int64_t beg = static_cast<int64_t>(blockIdx.x) * chunk;
+    const double inv = 1.0 / scale;
+    const int64_t beg = static_cast<int64_t>(lb) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
     double acc = 0.0;
+#pragma unroll 2
     for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
         double pc, yy, dinv;
-        op.apply(z, c, pc, yy, dinv);
+        op.apply(w, c, pc, yy, dinv);
+        yy *= inv;
         y[c] = yy;
-        acc += pc * yy;
+        acc += pc * inv * yy;
     }
-    block_partial(acc, part + blockIdx.x);
+    block_partial(acc, pout + lb);
 }
 
-// w = M^{-1} y - alpha_j z_j - beta_j z_{j-1} (in place of y) and partial
-// sums of ||w||_M^2.
-__global__ __launch_bounds__(kBlock) void k_lz_orth(const LzState *__restrict__ ls, Diag dg,
-                                                    double *__restrict__ y, const double *__restrict__ z,
-                                                    const double *__restrict__ zprev, const double *__restrict__ ab,
-                                                    int j, int steps, double *__restrict__ part, int64_t n,
-                                                    int64_t chunk)
+// w_{j+1} = M^{-1} y - alpha_j z_j - beta_j z_{j-1} (in place of y) and
+// partial sums of ||w_{j+1}||_M^2; alpha_j is the sum of the last partials,
+// recorded by the first block.  wprev is null for j = 0.
+__global__ __launch_bounds__(kBlock) void k_lz_orth(LzState *__restrict__ ls, Diag dg, double *__restrict__ y,
+                                                    const double *__restrict__ w, const double *__restrict__ wprev,
+                                                    const double *__restrict__ pin, double *__restrict__ pout,
+                                                    double *__restrict__ ab, int j, int steps, int cnt,
+                                                    uint32_t per, int64_t n, int64_t chunk)
 {
-    if (ls->stopped)
-        return;
-    const double aj = ab[j];
-    const double bj = j > 0 ? ab[steps + j - 1] : 0.0;
-    const int64_t beg = static_cast<int64_t>(blockIdx.x) * chunk;
+    const uint32_t lb = xcd_block(blockIdx.x, per);
+    if (ls->stopped || lb >= static_cast<uint32_t>(cnt))
+        return;  // whole block
+    const double alpha = sum_partials(pin, cnt);
+    if (lb == 0 && threadIdx.x == 0) {
+        ab[j] = alpha;
+        ls->amax = fmax(ls->amax, fabs(alpha));
+    }
+    const double sj = j > 0 ? ab[steps + j - 1] : ls->scale;  // z_j = w_j / sj
+    const double ca = alpha / sj;
+    const double cb = j > 1 ? sj / ab[steps + j - 2] : j == 1 ? sj / ls->scale : 0.0;
+    const int64_t beg = static_cast<int64_t>(lb) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
     double acc = 0.0;
-    for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
+    auto point = [&](int64_t c, double zp) {
         double d, di;
         dg.at(c, d, di);
-        const double zp = j > 0 ? zprev[c] : 0.0;
-        const double w = di * y[c] - aj * z[c] - bj * zp;
-        y[c] = w;
-        acc += d * w * w;
-    }
-    block_partial(acc, part + blockIdx.x);
-}
-
-// The fixed-order sum of the block partials and what follows from it:
-//   kind 0: ||u||_M (start vector): scale = it, stop with m = 0 unless > 0;
-//   kind 1: alpha_j = the sum, amax = max(amax, |alpha_j|);
-//   kind 2: beta_{j+1} = sqrt(sum), scale = beta_{j+1}, m = j + 1, stop when
-//           beta_{j+1} <= 1e-13 amax or not finite.
-__global__ __launch_bounds__(kSumThreads) void k_lz_sum(LzState *__restrict__ ls, const double *__restrict__ part,
-                                                        int cnt, int kind, int j, int steps,
-                                                        double *__restrict__ ab)
-{
-    if (ls->stopped)
-        return;
-    const double v = fixed_order_sum(part, cnt);
-    if (threadIdx.x != 0)
-        return;
-    if (kind == 0) {
-        const double un = sqrt(v);
-        ls->scale = un;
-        ls->m = 0;
-        ls->amax = 0.0;
-        if (!(un > 0.0) || !isfinite(un))
-            ls->stopped = 1;
-    } else if (kind == 1) {
-        ab[j] = v;
-        ls->amax = fmax(ls->amax, fabs(v));
-    } else {
-        const double bn = sqrt(v);
-        ab[steps + j] = bn;
-        ls->scale = bn;
-        ls->m = j + 1;
-        if (!(bn > 1e-13 * ls->amax) || !isfinite(bn))
-            ls->stopped = 1;
-    }
+        const double v = di * y[c] - ca * w[c] - zp;
+        y[c] = v;
+        acc += d * v * v;
+    };
+    if (j > 0)
+#pragma unroll 4
+        for (int64_t c = beg + threadIdx.x; c < end; c += kBlock)
+            point(c, cb * wprev[c]);
+    else
+#pragma unroll 4
+        for (int64_t c = beg + threadIdx.x; c < end; c += kBlock)
+            point(c, 0.0);
+    block_partial(acc, pout + lb);
 }
 
 // Number of eigenvalues of T_m below x (Sturm count: negative pivots of the
@@ -183,21 +204,34 @@ __device__ int sturm_count(const double *al, const double *be, int m, double x, 
     return cnt;
 }
 
-// Ritz values of T_m, ascending: lane k bisects for the k-th smallest
-// eigenvalue inside the Gershgorin interval of T_m until the interval can
-// no longer be halved in FP64.
-__global__ __launch_bounds__(kWave) void k_lz_ritz(const LzState *__restrict__ ls, const double *__restrict__ ab,
-                                                   int steps, double *__restrict__ ritz)
+// Ritz values of T_m, ascending: block k (one wave) narrows the Gershgorin
+// interval of T_m to the k-th smallest eigenvalue until the interval can no
+// longer be divided in FP64.  A section is 64 points, one a lane: 9 or 10
+// chains of divisions instead of the 53 of a bisection.  The first block also
+// records the last beta, summed like the others by all its waves: the digits
+// of a step do not depend on how many follow.
+__global__ __launch_bounds__(kBlock) void k_lz_ritz(LzState *__restrict__ ls, const double *__restrict__ pin, int cnt,
+                                                   double *__restrict__ ab, int steps, double *__restrict__ ritz)
 {
     __shared__ double al[kMaxLanczos], be[kMaxLanczos];
-    const int m = ls->m;
-    for (int i = threadIdx.x; i < m; i += kWave) {
-        al[i] = ab[i];
-        be[i] = ab[steps + i];
+    const int lane = threadIdx.x, k = blockIdx.x;  // the first wave divides
+    const int stopped = ls->stopped;
+    const int m = stopped ? ls->m : steps;
+    if (k == 0 && !stopped) {
+        const double beta = sqrt(sum_partials(pin, cnt));
+        if (lane == 0) {
+            ab[2 * steps - 1] = beta;
+            ls->m = steps;
+        }
+    }
+    if (k >= m)
+        return;
+    if (lane < m) {
+        al[lane] = ab[lane];
+        be[lane] = lane + 1 < m ? ab[steps + lane] : 0.0;
     }
     __syncthreads();
-    const int k = threadIdx.x;
-    if (k >= m)
+    if (lane >= kWave)
         return;
     double lo = al[0], hi = al[0], tmax = 0.0;
     for (int i = 0; i < m; ++i) {
@@ -207,16 +241,20 @@ __global__ __launch_bounds__(kWave) void k_lz_ritz(const LzState *__restrict__ l
         tmax = fmax(tmax, fabs(al[i]) + r);
     }
     const double pivmin = 1e-300 + 4.0 * 2.2250738585072014e-308 * fmax(1.0, tmax * tmax);
-    for (int it = 0; it < 200; ++it) {
+    for (int it = 0; it < 64; ++it) {
         const double mid = 0.5 * (lo + hi);
-        if (mid <= lo || mid >= hi)
+        if (!(mid > lo && mid < hi))
             break;
-        if (sturm_count(al, be, m, mid, pivmin) <= k)
-            lo = mid;
-        else
-            hi = mid;
+        // ascending; the middle lane takes the midpoint itself, so that every section divides the interval
+        const double x = lane == kWave / 2 ? mid : lo + (hi - lo) * ((lane + 0.5) / (kWave + 1));
+        const uint64_t above = __ballot(sturm_count(al, be, m, x, pivmin) > k);
+        const int f = above ? __builtin_ctzll(above) : kWave;  // first point above the eigenvalue
+        const double xl = __shfl(x, f > 0 ? f - 1 : 0), xh = __shfl(x, f < kWave ? f : 0);
+        lo = f > 0 ? xl : lo;
+        hi = f < kWave ? xh : hi;
     }
-    ritz[k] = 0.5 * (lo + hi);
+    if (lane == 0)
+        ritz[k] = 0.5 * (lo + hi);
 }
 
 Diag diag_of(const OpDev &op)
@@ -233,9 +271,11 @@ Diag diag_of(const OpDev &op)
 }
 
 template <class Op>
-hipError_t apply_step(const LzArgs &l, const Op &op, const double *z, double *y, hipStream_t st)
+hipError_t apply_step(const LzArgs &l, const Op &op, const double *w, double *y, int j, int steps, uint32_t per,
+                      hipStream_t st)
 {
-    hipLaunchKernelGGL((k_lz_apply<Op>), dim3(l.nb), dim3(kBlock), 0, st, l.ls, op, z, y, l.part, l.n, l.chunk);
+    hipLaunchKernelGGL((k_lz_apply<Op>), dim3(per * kNumXcd), dim3(kBlock), 0, st, l.ls, w, y, l.part + l.nb, l.part,
+                       l.ab, j, steps, l.nb, per, l.n, l.chunk, op);
     return hipGetLastError();
 }
 
@@ -244,40 +284,33 @@ hipError_t apply_step(const LzArgs &l, const Op &op, const double *z, double *y,
 hipError_t launch_lanczos(const LzArgs &l, const OpDev &op, const double *u, int steps, hipStream_t st)
 {
     const Diag dg = diag_of(op);
-    const uint32_t pts = static_cast<uint32_t>((l.n + kBlock - 1) / kBlock);
-    double *zprev = l.v[0], *z = l.v[1], *y = l.v[2];
-    hipLaunchKernelGGL(k_lz_norm0, dim3(l.nb), dim3(kBlock), 0, st, l.ls, dg, u, l.part, l.n, l.chunk);
-    hipLaunchKernelGGL(k_lz_sum, dim3(1), dim3(kSumThreads), 0, st, l.ls, l.part, l.nb, 0, 0, steps, l.ab);
-    hipLaunchKernelGGL(k_lz_scale, dim3(pts), dim3(kBlock), 0, st, l.ls, u, z, l.n);
+    const uint32_t per = (static_cast<uint32_t>(l.nb) + kNumXcd - 1) / kNumXcd;
+    double *const pb = l.part + l.nb;  // partials of the norms; those of alpha are at l.part
+    const double *wprev = nullptr, *w = u;
+    hipLaunchKernelGGL(k_lz_norm0, dim3(l.nb), dim3(kBlock), 0, st, dg, u, pb, l.n, l.chunk);
     for (int j = 0; j < steps; ++j) {
+        double *y = l.v[j % 3];  // w_{j-1} and w_j are in the other two, or u
         hipError_t e;
         if (op.kind == kOpPoisson)
-            e = apply_step(l, make_poisson<double>(op), z, y, st);
+            e = apply_step(l, make_poisson<double>(op), w, y, j, steps, per, st);
         else if (op.kind == kOpPoisson27)
-            e = apply_step(l, make_poisson27<double>(op), z, y, st);
+            e = apply_step(l, make_poisson27<double>(op), w, y, j, steps, per, st);
         else if (op.kind == kOpFaces)
-            e = apply_step(l, Ops<double>::faces(op), z, y, st);
+            e = apply_step(l, Ops<double>::faces(op), w, y, j, steps, per, st);
         else if (op.ell_slice && ell_keep(op, 8))
-            e = apply_step(l, Ops<double>::ell<true>(op), z, y, st);
+            e = apply_step(l, Ops<double>::ell<true>(op), w, y, j, steps, per, st);
         else if (op.ell_slice)
-            e = apply_step(l, Ops<double>::ell<false>(op), z, y, st);
+            e = apply_step(l, Ops<double>::ell<false>(op), w, y, j, steps, per, st);
         else
-            e = apply_step(l, Ops<double>::csr(op), z, y, st);
+            e = apply_step(l, Ops<double>::csr(op), w, y, j, steps, per, st);
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL(k_lz_sum, dim3(1), dim3(kSumThreads), 0, st, l.ls, l.part, l.nb, 1, j, steps, l.ab);
-        hipLaunchKernelGGL(k_lz_orth, dim3(l.nb), dim3(kBlock), 0, st, l.ls, dg, y, z, zprev, l.ab, j, steps,
-                           l.part, l.n, l.chunk);
-        hipLaunchKernelGGL(k_lz_sum, dim3(1), dim3(kSumThreads), 0, st, l.ls, l.part, l.nb, 2, j, steps, l.ab);
-        if (j + 1 < steps) {
-            // z_{j+1} = w / beta_{j+1} into the buffer of z_{j-1}; rotate
-            hipLaunchKernelGGL(k_lz_scale, dim3(pts), dim3(kBlock), 0, st, l.ls, y, zprev, l.n);
-            double *t = zprev;
-            zprev = z;
-            z = t;
-        }
+        hipLaunchKernelGGL(k_lz_orth, dim3(per * kNumXcd), dim3(kBlock), 0, st, l.ls, dg, y, w, wprev, l.part, pb,
+                           l.ab, j, steps, l.nb, per, l.n, l.chunk);
+        wprev = w;
+        w = y;
     }
-    hipLaunchKernelGGL(k_lz_ritz, dim3(1), dim3(kWave), 0, st, l.ls, l.ab, steps, l.ab + 2 * steps);
+    hipLaunchKernelGGL(k_lz_ritz, dim3(steps), dim3(kBlock), 0, st, l.ls, pb, l.nb, l.ab, steps, l.ab + 2 * steps);
     return hipGetLastError();
 }
 

@@ -216,15 +216,15 @@ hipError_t launch_bupdate(const BatchArgs &a, hipStream_t st);
 // Lanczos spectrum estimate (kernels_lanczos.hip).
 constexpr int kMaxLanczos = 64;  // largest number of Lanczos steps
 struct LzState {
-    double scale;  // ||u||_M, then the last beta_{j+1}
+    double scale;  // ||u||_M
     double amax;   // max |alpha_i| so far
     int32_t m;     // completed steps
     int32_t stopped;
 };
 struct LzArgs {
     LzState *ls = nullptr;
-    double *v[3] = {nullptr, nullptr, nullptr};  // z_{j-1}, z_j, y / w: n doubles each
-    double *part = nullptr;                      // block partials [nb]
+    double *v[3] = {nullptr, nullptr, nullptr};  // w_{j-1}, w_j, y / w_{j+1}: n doubles each
+    double *part = nullptr;                      // block partials [2 nb]: alpha, then the norms
     double *ab = nullptr;                        // alpha [steps], beta [steps], Ritz values [steps]
     int64_t n = 0, chunk = 0;
     int nb = 0;
