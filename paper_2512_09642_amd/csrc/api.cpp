@@ -1650,16 +1650,6 @@ static sstep_status setup_batched_impl(sstep_ctx *ctx, int32_t nsys, const sstep
                 HIPCHK(ctx, launch_to_fp32(dv, dv32, S.n, ctx->stream));
                 S.kx32 = k32, S.ky32 = k32 + nfx, S.kz32 = k32 + nfx + nfy, S.dvec32 = dv32;
             }
-            if (a.rec && o.basis_steps == 0) {  // Jacobi weights for the two-step basis
-                double *di = nullptr;
-                float *di32 = nullptr;
-                OKCHK(dalloc(ctx, &di, size_t(S.ld)));
-                if (a.fp32)
-                    OKCHK(dalloc(ctx, &di32, size_t(S.ld)));
-                S.dinv = di;
-                S.dinv32 = di32;
-                HIPCHK(ctx, launch_bdinv(S, o.precond, a.fp32, di, di32, ctx->stream));
-            }
         }
         B.sys.push_back(S);
         B.n.push_back(S.n);

@@ -134,8 +134,6 @@ struct BSys {
     const float *kx32, *ky32, *kz32;
     const double *dvec;              // M diagonal, zero-padded to ld
     const float *dvec32;
-    const double *dinv;              // Jacobi weights 1 / diag (1 without Jacobi), faces only
-    const float *dinv32;             // the same from the FP32 faces (FP32+IR)
     double theta, sigma, inv_sqrt_n;
     int64_t gchunk;                  // rows per chunk tile (multiple of kPad)
     int64_t gofs;                    // Gram partials of pair (q, r): gofs + r*E*nch
@@ -208,7 +206,6 @@ hipError_t launch_bp0scale(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bbasis(const BatchArgs &a, int j, hipStream_t st);
 hipError_t launch_bres_f2(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bbasis_pair(const BatchArgs &a, int j, hipStream_t st);
-hipError_t launch_bdinv(const BSys &S, int precond, int fp32, double *dinv, float *dinv32, hipStream_t st);
 hipError_t launch_bgram(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bfgs(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bupdate(const BatchArgs &a, hipStream_t st);
