@@ -1397,6 +1397,8 @@ static hipError_t enqueue_batched_iteration(const BatchArgs &a, hipStream_t s)
     // its ||r||^2 per band (beside the basis products in the moments kind)
     if ((e = a.bres ? launch_bres_f2(a, s) : launch_bresidual(a, s, true)) != hipSuccess)
         return e;
+    if ((e = launch_bstop(a, s)) != hipSuccess)
+        return e;
     int j = 0;
     if (a.f2)  // two steps per launch, an odd last step alone
         for (; j + 2 <= a.s; j += 2)

@@ -7,13 +7,6 @@
 
 namespace sstep {
 
-// A pair has stopped: counted once, by one thread.
-__device__ __forceinline__ void pair_stopped(BGlob *gl, const BSys &Q)
-{
-    atomicAdd(&gl->ndone, 1);
-    atomicAdd(&gl->bdone, Q.nbl);
-}
-
 // Gram partials of every active pair: tile (q, chunk, r) reduces rows
 // [chunk*gchunk, (chunk+1)*gchunk) of pair (q, r)'s basis (column stride
 // nrhs*ld, zero padding past n) into gpart[gofs + r*E*nch + e*nch + chunk].
@@ -112,15 +105,14 @@ hipError_t bgram_sym_launch_s(const BatchArgs &a, hipStream_t st)
     return hipGetLastError();
 }
 
-// One block (four waves) per pair: fixed-order sums of the pair's partials,
-// then wave 0 runs the stopping test, scaling and FGS; a pair that stops is
-// counted in the global done counter.
+// One block (four waves) per pair that k_bstop lets continue: fixed-order sums
+// of the pair's partials, then wave 0 runs scaling and FGS; a pair that breaks
+// down there is counted in the global done counter.
 constexpr int kBFgsThreads = 256;
 
 template <int S>
 __global__ __launch_bounds__(kBFgsThreads) void k_bfgs(BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                        DevState *__restrict__ pairs, int nrhs,
-                                                       const double *__restrict__ rpart,
                                                        const double *__restrict__ gpart, int nu, double cscale,
                                                        int fp32, double *__restrict__ dbg)
 {
@@ -131,12 +123,11 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs(BGlob *__restrict__ gl, c
         return;
     const BSys &Q = sys[p / nrhs];
     const int r = p % nrhs;
-    __shared__ double sg[E + 1];
+    __shared__ double sg[E];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const double *gp = gpart + Q.gofs + static_cast<int64_t>(r) * E * Q.nch;
-    const double *rp = rpart + Q.rofs + static_cast<int64_t>(r) * Q.nch;
-    for (int t = wave; t <= E; t += kBFgsThreads / kWave) {
-        const double *src = t < E ? gp + static_cast<int64_t>(t) * Q.nch : rp;
+    for (int t = wave; t < E; t += kBFgsThreads / kWave) {
+        const double *src = gp + static_cast<int64_t>(t) * Q.nch;
         double a0 = 0.0, a1 = 0.0;
         int q = lane;
         for (; q + kWave < Q.nch; q += 2 * kWave) {
@@ -149,17 +140,11 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs(BGlob *__restrict__ gl, c
         if (lane == 0)
             sg[t] = acc;
     }
-    __shared__ int stopped;
-    __syncthreads();
-    double *pdbg = dbg + static_cast<int64_t>(p) * dbg_size(S);
-    if (threadIdx.x == 0)
-        stopped = stop_test(ps, sg[E], pdbg + dbg_rho(S), nullptr, 0);
     __syncthreads();
     if (wave != 0)
         return;
-    int now = stopped;
-    if (!now)
-        now = fgs_wave<S>(ps, sg, nu, cscale, fp32, Q.inv_sqrt_n, pdbg, nullptr, 0);
+    double *pdbg = dbg + static_cast<int64_t>(p) * dbg_size(S);
+    const int now = fgs_wave<S>(ps, sg, nu, cscale, fp32, Q.inv_sqrt_n, pdbg, nullptr, 0);
     if (now && lane == 0)
         pair_stopped(gl, Q);
 }
@@ -167,8 +152,8 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs(BGlob *__restrict__ gl, c
 template <int S>
 hipError_t bfgs_launch_s(const BatchArgs &a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_bfgs<S>, dim3(a.npairs), dim3(kBFgsThreads), 0, st, a.gl, a.sys, a.pairs, a.nrhs, a.rpart,
-                       a.gpart, a.nu, a.cscale, a.fp32, a.dbg);
+    hipLaunchKernelGGL(k_bfgs<S>, dim3(a.npairs), dim3(kBFgsThreads), 0, st, a.gl, a.sys, a.pairs, a.nrhs, a.gpart,
+                       a.nu, a.cscale, a.fp32, a.dbg);
     return hipGetLastError();
 }
 
@@ -202,37 +187,30 @@ __device__ __forceinline__ void bfgs_map_sweep(BGlob *__restrict__ gl, DevState 
         pair_stopped(gl, Q);
 }
 
-// Recurrence Gram kind: the pair's sums of H and c', the stopping test, then
-// H mapped onto G_raw = P^T A P with the system's theta, sigma (as k_fgs_rec
+// Recurrence Gram kind: the pair's sums of H and c', then H mapped onto G_raw = P^T A P with the system's theta, sigma (as k_fgs_rec
 // does) and the FGS wave.
 template <int S>
 __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_rec(BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                            DevState *__restrict__ pairs, int nrhs,
-                                                           const double *__restrict__ rpart,
-                                                           const double *__restrict__ bpart,
                                                            const double *__restrict__ gpart, int nu, double cscale,
                                                            int fp32, double hscale, double *__restrict__ dbg)
 {
     constexpr int S1 = S + 1;
     constexpr int E1 = S1 * (S1 + 1) / 2 + S1;
     constexpr int T0 = S * (S + 1) / 2;
-    // ||r||^2: one partial per band (bpart, k_bres_f2, one slot per
-    // right-hand side) or per chunk tile (rpart, k_bresidual)
     const int p = blockIdx.x;
     DevState *ps = pairs + p;
     if (ps->done)
         return;
     const BSys &Q = sys[p / nrhs];
     const int r = p % nrhs;
-    __shared__ double h[E1 + 1];
+    __shared__ double h[E1];
     __shared__ double sg[T0 + S];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const double *gp = gpart + Q.gofs + static_cast<int64_t>(r) * E1 * Q.nch;
-    const double *rp = bpart ? bpart + Q.mofs + static_cast<int64_t>(r) * Q.nf2q
-                             : rpart + Q.rofs + static_cast<int64_t>(r) * Q.nch;
-    for (int t = wave; t <= E1; t += kBFgsThreads / kWave) {
-        const double *src = t < E1 ? gp + static_cast<int64_t>(t) * Q.nch : rp;
-        const int cnt = t < E1 || !bpart ? Q.nch : Q.nf2q;
+    for (int t = wave; t < E1; t += kBFgsThreads / kWave) {
+        const double *src = gp + static_cast<int64_t>(t) * Q.nch;
+        const int cnt = Q.nch;
         double a0 = 0.0, a1 = 0.0;
         int q = lane;
         for (; q + kWave < cnt; q += 2 * kWave) {
@@ -245,17 +223,8 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_rec(BGlob *__restrict__ g
         if (lane == 0)
             h[t] = acc;
     }
-    __shared__ int stopped;
     __syncthreads();
     double *pdbg = dbg + static_cast<int64_t>(p) * dbg_size(S);
-    if (threadIdx.x == 0)
-        stopped = stop_test(ps, h[E1], pdbg + dbg_rho(S), nullptr, 0);
-    __syncthreads();
-    if (stopped) {
-        if (threadIdx.x == 0)
-            pair_stopped(gl, Q);
-        return;
-    }
     bfgs_map_sweep<S>(gl, ps, Q, h, sg, nu, cscale, fp32, hscale, pdbg);
 }
 
@@ -263,15 +232,13 @@ template <int S>
 hipError_t bfgs_rec_launch_s(const BatchArgs &a, hipStream_t st)
 {
     hipLaunchKernelGGL(k_bfgs_rec<S>, dim3(a.npairs), dim3(kBFgsThreads), 0, st, a.gl, a.sys, a.pairs, a.nrhs,
-                       a.rpart, a.bres && !a.mom ? a.mpart : nullptr, a.gpart, a.nu, a.cscale, a.fp32,
-                       a.rec_hscale, a.dbg);
+                       a.gpart, a.nu, a.cscale, a.fp32, a.rec_hscale, a.dbg);
     return hipGetLastError();
 }
 
 // Moments kind: per pair, the sums of its 2S + 1 product slots (one partial
-// per band of its system, written by the two-step basis) and of its residual
-// partials, the stopping test, then the moments, H (as k_fgs_mom forms them)
-// and the recurrence mapping with the FGS wave.
+// per band of its system, written by the two-step basis), then the moments, H
+// (as k_fgs_mom forms them) and the recurrence mapping with the FGS wave.
 template <int S>
 __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_mom(BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                            DevState *__restrict__ pairs, int nrhs,
@@ -288,14 +255,14 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_mom(BGlob *__restrict__ g
         return;
     const BSys &Q = sys[p / nrhs];
     const int r = p % nrhs;
-    __shared__ double m[NS + 1];
+    __shared__ double m[NS];
     __shared__ double mu[NS];
     __shared__ double h[E1];
     __shared__ double sg[T0 + S];
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    // slots 0 .. NS - 1: the products; slot NS: ||r||^2 (k_bres_f2)
+    // slots 0 .. NS - 1: the products (slot NS: ||r||^2, k_bres_f2)
     const double *mp = mpart + Q.mofs + static_cast<int64_t>(r) * bmom_slots(S) * Q.nf2q;
-    for (int t = wave; t <= NS; t += kBFgsThreads / kWave) {
+    for (int t = wave; t < NS; t += kBFgsThreads / kWave) {
         const double *src = mp + static_cast<int64_t>(t) * Q.nf2q;
         const int cnt = Q.nf2q;
         double a0 = 0.0, a1 = 0.0;
@@ -310,17 +277,8 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_mom(BGlob *__restrict__ g
         if (lane == 0)
             m[t] = acc;
     }
-    __shared__ int stopped;
     __syncthreads();
     double *pdbg = dbg + static_cast<int64_t>(p) * dbg_size(S);
-    if (threadIdx.x == 0)
-        stopped = stop_test(ps, m[NS], pdbg + dbg_rho(S), nullptr, 0);
-    __syncthreads();
-    if (stopped) {
-        if (threadIdx.x == 0)
-            pair_stopped(gl, Q);
-        return;
-    }
     for (int k = threadIdx.x; k < NS; k += kBFgsThreads)
         mu[k] = k <= 1 ? m[k] : 2.0 * m[k] - m[k % 2];
     __syncthreads();

@@ -120,6 +120,51 @@ hipError_t launch_bgram(const BatchArgs &a, hipStream_t st)
 #undef SSTEP_BG
 }
 
+namespace {
+// The stopping test of every pair that still runs, a wave each, between its
+// residual and its basis: a pair that stops forms no basis for it.  ||r||^2
+// has one partial per band (bpart, k_bres_f2) or per chunk tile (rpart,
+// k_bresidual); a pair that stops is counted in the global done counter.
+//
+// With the test behind the basis, in the FGS launch, every pair's last
+// residual was followed by a whole basis: 4.0 of 28.1 ms for 4 outer
+// iterations of 20 systems of 32^3 to 96^3 with 8 right-hand sides (23.7 now),
+// 80 of 1180 us for 6 of 12 systems of 9^3 to 33^3 with 3.
+__global__ __launch_bounds__(kBlock) void k_bstop(BGlob *__restrict__ gl, const BSys *__restrict__ sys,
+                                                  DevState *__restrict__ pairs, int npairs, int nrhs,
+                                                  const double *__restrict__ rpart, const double *__restrict__ bpart,
+                                                  int slots, int slot, int s, double *__restrict__ dbg)
+{
+    const int p = blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    if (p >= npairs || pairs[p].done)
+        return;  // the whole wave
+    const BSys &Q = sys[p / nrhs];
+    const int r = p % nrhs;
+    const double *src = bpart ? bpart + Q.mofs + (static_cast<int64_t>(r) * slots + slot) * Q.nf2q
+                              : rpart + Q.rofs + static_cast<int64_t>(r) * Q.nch;
+    const int cnt = bpart ? Q.nf2q : Q.nch;
+    double a0 = 0.0, a1 = 0.0;
+    int q = lane;
+    for (; q + kWave < cnt; q += 2 * kWave) {
+        a0 += src[q];
+        a1 += src[q + kWave];
+    }
+    for (; q < cnt; q += kWave)
+        a0 += src[q];
+    const double rho2 = wave_sum(a0 + a1);
+    if (lane == 0 && stop_test(pairs + p, rho2, dbg + static_cast<int64_t>(p) * dbg_size(s) + dbg_rho(s), nullptr, 0))
+        pair_stopped(gl, Q);
+}
+}  // namespace
+
+hipError_t launch_bstop(const BatchArgs &a, hipStream_t st)
+{
+    constexpr int per = kBlock / kWave;
+    hipLaunchKernelGGL(k_bstop, dim3((a.npairs + per - 1) / per), dim3(kBlock), 0, st, a.gl, a.sys, a.pairs, a.npairs,
+                       a.nrhs, a.rpart, a.bres ? a.mpart : nullptr, a.bres_slots, a.bres_slot, a.s, a.dbg);
+    return hipGetLastError();
+}
+
 hipError_t launch_bfgs(const BatchArgs &a, hipStream_t st)
 {
     if (a.mom) {

@@ -207,6 +207,7 @@ hipError_t launch_bbasis(const BatchArgs &a, int j, hipStream_t st);
 hipError_t launch_bres_f2(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bbasis_pair(const BatchArgs &a, int j, hipStream_t st);
 hipError_t launch_bgram(const BatchArgs &a, hipStream_t st);
+hipError_t launch_bstop(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bfgs(const BatchArgs &a, hipStream_t st);
 hipError_t launch_bupdate(const BatchArgs &a, hipStream_t st);
 

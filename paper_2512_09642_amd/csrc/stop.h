@@ -138,4 +138,11 @@ __device__ __forceinline__ int stop_at_head(DevState *st, const StopArgs &a, dou
     return r.stop;
 }
 
+// A pair of a batch has stopped: counted once, by one thread.
+__device__ __forceinline__ void pair_stopped(BGlob *gl, const BSys &Q)
+{
+    atomicAdd(&gl->ndone, 1);
+    atomicAdd(&gl->bdone, Q.nbl);
+}
+
 }  // namespace sstep
