@@ -3,6 +3,7 @@
 // All of them are bound by HBM bandwidth (well under one flop per byte).
 #include <algorithm>
 
+#include "band_f2.h"
 #include "launch.h"
 #include "march.h"
 #include "opsel.h"
@@ -757,12 +758,81 @@ bool f2_box(const IterArgs &a) { return a.op.kind == kOpPoisson27; }
 
 F2Plan f2_plan(const IterArgs &a) { return plan_f2(a.op.g, f2_box(a), a.fp32 ? 4 : 8); }
 
-// The two-step kernel serves the Chebyshev basis of the constant operators
-// when AP is not stored (moments, recurrence and operator-applying Gram
-// kinds).
+// Bands of a face-coefficient system for the two-step basis (band_f2.h): rows
+// as the batch splits them (bands.h), planes by the cost of plan_f2.
+struct BandPlan {
+    int h, kz;  // rows of a band, planes of a range
+    uint32_t bands, ranges, nbl, per;
+};
+BandPlan plan_bands(const Grid3 &g)
+{
+    BandPlan p{};
+    const int inner = static_cast<int>(kBf2Threads / g.nx) - 2;  // band rows a block can hold
+    p.bands = g.nxy <= kBf2Threads ? 1u : inner < 1 ? 0u : static_cast<uint32_t>((g.ny + inner - 1) / inner);
+    if (!p.bands)
+        return p;
+    p.h = (g.ny + static_cast<int>(p.bands) - 1) / static_cast<int>(p.bands);
+    p.bands = static_cast<uint32_t>((g.ny + p.h - 1) / p.h);
+    int64_t best = INT64_MAX;
+    for (int kz = 1; kz <= kBf2MaxPlanes && kz <= g.nz; ++kz) {
+        const int64_t nbl = static_cast<int64_t>(p.bands) * ((g.nz + kz - 1) / kz);
+        const int64_t cost = (nbl + kF2Cus - 1) / kF2Cus * (kz + 2 + 2);
+        if (cost < best)
+            best = cost, p.kz = kz;
+    }
+    p.ranges = static_cast<uint32_t>((g.nz + p.kz - 1) / p.kz);
+    p.nbl = p.bands * p.ranges;
+    p.per = (p.nbl + kNumXcd - 1) / kNumXcd;
+    return p;
+}
+
+// Two steps of a face-coefficient system's basis, FP64: block of a band and a
+// range, the bands of a range together on one XCD.
+template <bool FIRST, bool MOM>
+__global__ __launch_bounds__(kBf2Lanes) void k_basis_band(const DevState *__restrict__ st, BandArgs<double> a,
+                                                          BandPlan plan, double *__restrict__ mpart, int64_t mstride)
+{
+    if (st->done)
+        return;
+    const uint32_t lb = xcd_block(blockIdx.x, plan.per);
+    if (lb >= plan.nbl)
+        return;  // whole block
+    const int zr = static_cast<int>(lb / plan.bands), band = static_cast<int>(lb - zr * plan.bands);
+    const int y0 = band * plan.h, y1 = y0 + plan.h < a.ny ? y0 + plan.h : a.ny;
+    const int k0 = zr * plan.kz, k1 = k0 + plan.kz < a.nz ? k0 + plan.kz : a.nz;
+    band_pair<double, true, FIRST, 2, MOM, true>(a, y0, y1, k0, k1, MOM ? mpart + lb : nullptr, mstride);
+}
+
+// Face-coefficient systems that take two steps per launch (FP64): from kBandMin
+// unknowns, where two single steps begin to cost more than the chain of planes
+// of a pair (2 x 4.1 against 9.1 us at 64^3, 2 x 6.0 against 11.4 at 80^3,
+// 2 x 9.1 against 15.1 at 96^3, 2 x 19.4 against 26.5 at 128^3, 2 x 35 against
+// 50 at 160^3), and with rows of at most kBandRow points, four to a block, two
+// of them its own (2 x 34.5 against 58 us at 256 x 256 x 60, but 2 x 44
+// against 109 at 341 x 341 x 40, one row of three).  Stored through the
+// caches, which hold the columns of such a system for the next launch (128^3:
+// 30.0 us past them, 27.5 through).
+constexpr int64_t kBandMin = int64_t(1) << 19;
+constexpr int kBandRow = kBf2Threads / 4;
+bool band_pairs_apply(const IterArgs &a)
+{
+    const Grid3 &g = a.op.g;
+    if (a.op.kind != kOpFaces || a.fp32 || a.op.n < kBandMin || g.nx > kBandRow)
+        return false;
+    const int64_t nx = g.nx, ny = g.ny, nz = g.nz;
+    return 8 * std::max({nz * ny * (nx + 1), nz * (ny + 1) * nx, (nz + 1) * g.nxy}) <= kF2MaxWindow;
+}
+
+// The two-step kernels serve the Chebyshev basis of the constant operators and
+// of large face-coefficient systems when AP is not stored (moments, recurrence
+// and operator-applying Gram kinds).
 bool basis_pairs_apply(const IterArgs &a)
 {
-    if ((a.op.kind != kOpPoisson && a.op.kind != kOpPoisson27) || a.AP || a.monomial || a.one_step)
+    if (a.AP || a.monomial || a.one_step)
+        return false;
+    if (a.op.kind == kOpFaces)
+        return band_pairs_apply(a);
+    if (a.op.kind != kOpPoisson && a.op.kind != kOpPoisson27)
         return false;
     if (a.op.kind == kOpPoisson27 && a.op.n < kF2BoxMin)
         return false;
@@ -796,9 +866,27 @@ hipError_t basis_pair_v(const IterArgs &a, int j, hipStream_t st)
     return hipGetLastError();
 }
 
+template <bool MOM>
+hipError_t basis_band_v(const IterArgs &a, int j, hipStream_t st)
+{
+    const BandPlan plan = plan_bands(a.op.g);
+    double *pj = static_cast<double *>(a.P) + j * a.ld;
+    const BandArgs<double> b{a.op.g.nx, a.op.g.ny, a.op.g.nz, a.op.precond, a.theta,   a.sigma,       a.op.kx,
+                             a.op.ky,   a.op.kz,   pj,        pj - (j > 0 ? a.ld : 0), pj + a.ld, pj + 2 * a.ld};
+    double *mp = MOM ? a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride : nullptr;
+    const dim3 grid(plan.per * kNumXcd), block(kBf2Lanes);
+    if (j == 0)
+        hipLaunchKernelGGL((k_basis_band<true, MOM>), grid, block, 0, st, a.st, b, plan, mp, a.mstride);
+    else
+        hipLaunchKernelGGL((k_basis_band<false, MOM>), grid, block, 0, st, a.st, b, plan, mp, a.mstride);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t basis_pair(const IterArgs &a, int j, hipStream_t st)
 {
+    if (a.op.kind == kOpFaces)
+        return a.gram_mom ? basis_band_v<true>(a, j, st) : basis_band_v<false>(a, j, st);
     if constexpr (sizeof(T) == 8)  // the moments kind is FP64 only
         if (a.gram_mom)
             return f2_box(a) ? basis_pair_v<T, true, true>(a, j, st) : basis_pair_v<T, false, true>(a, j, st);
@@ -1105,7 +1193,7 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
     };
     int j = 0;
     if (basis_pairs_apply(a)) {
-        const int64_t nbl = f2_plan(a).nbl;
+        const int64_t nbl = a.op.kind == kOpFaces ? plan_bands(a.op.g).nbl : f2_plan(a).nbl;
         for (; j + 2 <= m; j += 2)
             put(j, 2, nbl);
     }
