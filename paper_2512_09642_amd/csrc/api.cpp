@@ -1415,12 +1415,11 @@ static hipError_t enqueue_batched_iteration(const BatchArgs &a, hipStream_t s)
 }
 
 // Times the launches of an outer iteration that the tile schedule sets (the
-// residual outside the moments kind, the single-step basis and the Gram
-// reduction when they run, the update) for each tile size and persistent-grid factor; keeps the
+// residual without a band table, the single-step basis and the Gram reduction,
+// as they run) for each tile size and persistent-grid factor; keeps the
 // fastest pair, cached like the single-system Gram schedule.  The residual
-// and the update run on zeroed scratch right-hand sides and iterates with
-// zero step lengths (x stays zero), freed before returning; without device
-// memory for them the default schedule stays.
+// runs on zeroed scratch right-hand sides and iterates, freed before
+// returning; without device memory for them the default schedule stays.
 static sstep_status tune_batched(sstep_ctx *ctx)
 {
     Batched &B = *ctx->batch;
@@ -1477,9 +1476,7 @@ static sstep_status tune_batched(sstep_ctx *ctx)
             return e;
         if (!a.f2 && (e = launch_bbasis(a, 1 < a.s ? 1 : 0, ctx->stream)) != hipSuccess)
             return e;
-        if ((e = launch_bgram(a, ctx->stream)) != hipSuccess)
-            return e;
-        return launch_bupdate(a, ctx->stream);
+        return launch_bgram(a, ctx->stream);
     };
     int64_t best_chunk = B.gchunk;
     int best_factor = B.grid_factor;

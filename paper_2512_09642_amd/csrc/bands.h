@@ -17,7 +17,7 @@ struct BF2Tile {
 };
 constexpr int kBf2Threads = 1024;    // threads per block of the two-step batched basis
 constexpr int kBf2MaxPlanes = 128;   // longest z-range of one block
-constexpr int kBf2MinPlanes = 16;    // shortest z-range (small batches, end of a solve)
+constexpr int kBf2MinPlanes = 16;    // z-range at the end of a solve; longest of a small batch
 constexpr int kBf2BlocksPerCu = 4;   // blocks per CU the longest ranges must still give
 constexpr uint32_t kBf2NoBlock = 0xFFFFFFFFu;  // dispatch entry past an XCD's queue
 
@@ -66,10 +66,14 @@ inline std::vector<BF2Tile> bf2_bands_kz(const std::vector<BandGrid> &grids, siz
 }
 
 // The longest z-ranges (at most kBf2MaxPlanes planes) that still give every
-// CU kBf2BlocksPerCu blocks, else ranges of kBf2MinPlanes: a long range
-// re-reads fewer halo planes and starts fewer blocks (the batched workload:
-// 2.10 s with whole-system ranges of up to 96 planes against 2.30 s with
-// 16), a short one keeps small batches spread over the chip.
+// CU kBf2BlocksPerCu blocks: a long range re-reads fewer halo planes and
+// starts fewer blocks (the batched workload: 2.10 s with whole-system ranges
+// of up to 96 planes against 2.30 s with 16).  A batch that gives fewer blocks
+// even with kBf2MinPlanes planes takes the length, up to that, with the
+// fewest plane steps: one block runs on a CU at a time, and a range of kz
+// planes is a chain of kz steps, two for the halo and about two to start
+// (12 systems of 9^3 to 33^3, 3 right-hand sides, FP32: a pair of steps 15.7
+// -> 11.3 us, the residual 16.0 -> 10.7, against ranges of 16).
 inline std::vector<BF2Tile> bf2_bands(const std::vector<BandGrid> &grids, size_t elem, bool faces, int nt, int nrhs,
                                       int cus)
 {
@@ -77,7 +81,16 @@ inline std::vector<BF2Tile> bf2_bands(const std::vector<BandGrid> &grids, size_t
     for (int kzt : {kBf2MaxPlanes, 96, 64, 48, 32, 24, kBf2MinPlanes}) {
         out = bf2_bands_kz(grids, elem, faces, nt, kzt);
         if (out.empty() || int64_t(out.size()) * nrhs >= int64_t(kBf2BlocksPerCu) * cus)
-            break;
+            return out;
+    }
+    auto cost = [&](const std::vector<BF2Tile> &tab, int kzt) {
+        return (int64_t(tab.size()) * nrhs + cus - 1) / cus * (kzt + 4);
+    };
+    int64_t best = cost(out, kBf2MinPlanes);
+    for (int kzt = kBf2MinPlanes - 1; kzt >= 2; --kzt) {
+        std::vector<BF2Tile> tab = bf2_bands_kz(grids, elem, faces, nt, kzt);
+        if (cost(tab, kzt) < best)
+            best = cost(tab, kzt), out = std::move(tab);
     }
     return out;
 }

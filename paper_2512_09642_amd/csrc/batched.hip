@@ -399,47 +399,51 @@ done:
                                  S.nf2q);
 }
 
-// x += P alpha for every pair whose solve continues.
+// acc = sum_i alpha_i p_i at one point: P is read once, non-temporal loads,
+// eight columns in flight at a time, summed in column order.
+template <typename T>
+__device__ __forceinline__ double basis_sum(const T *__restrict__ Pr, int64_t step, int64_t c, int s,
+                                            const double *__restrict__ alpha)
+{
+    double acc = 0.0;
+    int i = 0;
+    for (; i + 8 <= s; i += 8) {
+        T v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = __builtin_nontemporal_load(Pr + (i + u) * step + c);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            acc += static_cast<double>(v[u]) * alpha[i + u];
+    }
+    for (; i < s; ++i)
+        acc += static_cast<double>(__builtin_nontemporal_load(Pr + i * step + c)) * alpha[i];
+    return acc;
+}
+
+// x += P alpha for every pair whose solve continues: a block per kBlock points
+// of one pair, right-hand side after right-hand side.  HBM-bound: 20 systems of
+// 32^3 to 96^3, 8 right-hand sides, s = 16, FP64: 1440 us with chunk tiles of
+// 2048 rows or more that walk the right-hand sides, 1370 (5.6 TB/s) with these;
+// 12 systems of 9^3 to 33^3, 3 right-hand sides, FP32+IR, whose 70 tiles left
+// most CUs idle: 25.3 -> 6.2 us.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_bupdate(const BGlob *__restrict__ gl, const BSys *__restrict__ sys,
-                                                    const BTile *__restrict__ tiles, int ntiles,
+                                                    const PTile *__restrict__ tiles, uint32_t ntiles,
                                                     const DevState *__restrict__ pairs, int nrhs, int s,
                                                     const T *__restrict__ P)
 {
     if (gl->ndone == gl->npairs)
         return;
-    for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const BTile tl = tiles[t];
-        const BSys &S = sys[tl.q];
-        const int64_t beg = static_cast<int64_t>(tl.chunk) * S.gchunk;
-        const int64_t end = beg + S.gchunk < S.n ? beg + S.gchunk : S.n;
-        for (int r = 0; r < nrhs; ++r) {
-            const DevState &ps = pairs[S.pair0 + r];
-            if (ps.done)
-                continue;
-            double *__restrict__ x = ps.x;
-            const T *Pr = P + S.pofs + static_cast<int64_t>(r) * S.ld;
-            const int64_t step = static_cast<int64_t>(nrhs) * S.ld;
-            for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
-                // P is read once: non-temporal loads, eight columns in flight
-                // at a time, summed in column order
-                double acc = 0.0;
-                int i = 0;
-                for (; i + 8 <= s; i += 8) {
-                    T v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        v[u] = __builtin_nontemporal_load(Pr + (i + u) * step + c);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u)
-                        acc += static_cast<double>(v[u]) * ps.alpha[i + u];
-                }
-                for (; i < s; ++i)
-                    acc += static_cast<double>(__builtin_nontemporal_load(Pr + i * step + c)) * ps.alpha[i];
-                x[c] += acc;
-            }
-        }
-    }
+    const uint32_t r = blockIdx.x / ntiles;
+    const PTile tl = tiles[blockIdx.x - r * ntiles];
+    const BSys &S = sys[tl.q];
+    const DevState &ps = pairs[S.pair0 + r];
+    const int64_t c = static_cast<int64_t>(tl.blk) * kBlock + threadIdx.x;
+    if (ps.done || c >= S.n)
+        return;
+    ps.x[c] += basis_sum(P + S.pofs + static_cast<int64_t>(r) * S.ld, static_cast<int64_t>(nrhs) * S.ld, c, s,
+                         ps.alpha);
 }
 
 }  // namespace
@@ -559,12 +563,14 @@ hipError_t launch_bbasis_pair(const BatchArgs &a, int j, hipStream_t st)
 
 hipError_t launch_bupdate(const BatchArgs &a, hipStream_t st)
 {
+    const uint32_t npt = static_cast<uint32_t>(a.npt);
+    const dim3 grid(npt * static_cast<uint32_t>(a.nrhs));
     if (a.fp32)
-        hipLaunchKernelGGL(k_bupdate<float>, dim3(a.grid_bt), dim3(kBlock), 0, st, a.gl, a.sys, a.btiles, a.nbt,
-                           a.pairs, a.nrhs, a.s, static_cast<const float *>(a.P));
+        hipLaunchKernelGGL(k_bupdate<float>, grid, dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt, a.pairs, a.nrhs,
+                           a.s, static_cast<const float *>(a.P));
     else
-        hipLaunchKernelGGL(k_bupdate<double>, dim3(a.grid_bt), dim3(kBlock), 0, st, a.gl, a.sys, a.btiles, a.nbt,
-                           a.pairs, a.nrhs, a.s, static_cast<const double *>(a.P));
+        hipLaunchKernelGGL(k_bupdate<double>, grid, dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt, a.pairs, a.nrhs,
+                           a.s, static_cast<const double *>(a.P));
     return hipGetLastError();
 }
 

@@ -62,7 +62,8 @@ __device__ __forceinline__ Vec4<T> ld4(const T *p)
 // 16-byte aligned, rows multiples of 4, zero past the system), the block's
 // partial of entry e written to out[e * estride + slot].  Ends with a
 // barrier, so a block may call it again for another range.
-template <typename T, int S1, bool WAP, bool WD>
+// AHEAD: steps whose loads are issued together; the sums are the same.
+template <typename T, int S1, bool WAP, bool WD, int AHEAD = 1>
 __device__ __forceinline__ void gram_sym_rows(const T *__restrict__ P, int64_t cs, const T *__restrict__ dvec,
                                               int64_t beg, int64_t end, double *__restrict__ out, int64_t estride,
                                               int64_t slot)
@@ -85,48 +86,67 @@ __device__ __forceinline__ void gram_sym_rows(const T *__restrict__ P, int64_t c
 
     typename M::acc_t gacc = {}, bacc = {}, bbacc = {};
     T cacc = T(0), cbacc = T(0), hx = T(0), hxx = T(0), cx = T(0);
-    for (int64_t r0 = beg + wv * kGsRowsPerWave; r0 < end; r0 += kGsRowsPerStep) {
+    struct Rows {
+        Vec4<T> p, w, px, pb;
+    };
+    auto load = [&](int64_t r0) -> Rows {
         const int64_t row = r0 + 4 * gq;
-        const Vec4<T> p = ccol ? ld4(colp + row) : Vec4<T>{};
-        Vec4<T> w{}, px{}, pb{};
+        Rows v{};
+        v.p = ccol ? ld4(colp + row) : Vec4<T>{};
         if constexpr (WAP || WD)
-            w = ld4(dvec + row);
+            v.w = ld4(dvec + row);
         if constexpr (XC)
-            px = ld4(xcol + row);
+            v.px = ld4(xcol + row);
         if constexpr (TWO)
-            pb = bcol ? ld4(colb + row) : Vec4<T>{};
+            v.pb = bcol ? ld4(colb + row) : Vec4<T>{};
+        return v;
+    };
+    auto add = [&](const Rows &v) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const T a = p.v[t];
+            const T a = v.p.v[t];
             T b = a;
             if constexpr (WAP)
-                b *= w.v[t];
+                b *= v.w.v[t];
             gacc = M::step(a, b, gacc);  // H[A][A]
             T w0 = go_row_bcast0(a);     // p_0 at this row
             if constexpr (WD)
-                w0 *= w.v[t];
+                w0 *= v.w.v[t];
             cacc += a * w0;
             if constexpr (TWO) {
-                const T ab = pb.v[t];
+                const T ab = v.pb.v[t];
                 T bb = ab;
                 if constexpr (WAP)
-                    bb *= w.v[t];
+                    bb *= v.w.v[t];
                 bacc = M::step(ab, b, bacc);    // H[B][A]
                 bbacc = M::step(ab, bb, bbacc);  // H[B][B]
                 cbacc += ab * w0;
             }
             if constexpr (XC) {
-                T xw = px.v[t];
+                T xw = v.px.v[t];
                 if constexpr (WAP)
-                    xw *= w.v[t];
+                    xw *= v.w.v[t];
                 hx += a * xw;  // H[16][c]
                 if (c == 0) {
-                    hxx += px.v[t] * xw;  // H[16][16]
-                    cx += px.v[t] * w0;   // c'_16
+                    hxx += v.px.v[t] * xw;  // H[16][16]
+                    cx += v.px.v[t] * w0;   // c'_16
                 }
             }
         }
-    }
+    };
+    int64_t r0 = beg + wv * kGsRowsPerWave;
+    if constexpr (AHEAD > 1)
+        for (; r0 + (AHEAD - 1) * kGsRowsPerStep < end; r0 += AHEAD * kGsRowsPerStep) {
+            Rows v[AHEAD];
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                v[u] = load(r0 + u * kGsRowsPerStep);
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+                add(v[u]);
+        }
+    for (; r0 < end; r0 += kGsRowsPerStep)
+        add(load(r0));
 
     // per wave: the H blocks, c', column 16 into LDS; then the block's fixed-order sum
 #pragma unroll
