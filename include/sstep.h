@@ -291,9 +291,10 @@ int32_t sstep_gram_mode(const sstep_ctx *ctx);
  * (Sec. 2, Definition; m = s - 1 with SSTEP_GRAM_APPLY_OP, else s).  With
  * basis_steps = 0, for the constant 7-point operator (any size) and the
  * 27-point operator (327680 unknowns or more) with the Chebyshev basis and AP
- * not stored, for the 7-point face-coefficient operator in FP64 with 524288
- * unknowns or more and rows of at most 256 points (the same conditions), and
- * for batched stencil systems with the recurrence Gram kind, one launch forms
+ * not stored, for the 7-point face-coefficient operator in FP64 (the same
+ * conditions) with 524288 unknowns or more and rows of at most 256 points, or
+ * 2048 to 262144 unknowns and even s (not in grids so thin that their 8 x 8 x
+ * 8 bricks are mostly empty), and for batched stencil systems with the recurrence Gram kind, one launch forms
  * two consecutive columns (p_{j+1} and p_{j+2} from p_{j-1} and p_j, exactly
  * as two single steps would; a single face-coefficient system's up to the
  * rounding of the operator), and *pairs (if pairs

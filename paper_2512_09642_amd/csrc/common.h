@@ -108,15 +108,22 @@ __device__ __forceinline__ void swap_rows(uint32_t &a, uint32_t &b)
                               : __builtin_amdgcn_permlane16_swap(a, b, false, false);
     a = r[0], b = r[1];
 }
+// The same for two values at once: a's sums in the first half of the wave (row
+// of the half), b's in the second.
 template <int ROWS>
-__device__ __forceinline__ double add_rows(double v)
+__device__ __forceinline__ double add_rows(double a, double b)
 {
-    uint32_t l0 = static_cast<uint32_t>(__double2loint(v)), l1 = l0;
-    uint32_t h0 = static_cast<uint32_t>(__double2hiint(v)), h1 = h0;
+    uint32_t l0 = static_cast<uint32_t>(__double2loint(a)), l1 = static_cast<uint32_t>(__double2loint(b));
+    uint32_t h0 = static_cast<uint32_t>(__double2hiint(a)), h1 = static_cast<uint32_t>(__double2hiint(b));
     swap_rows<ROWS>(l0, l1);
     swap_rows<ROWS>(h0, h1);
     return __hiloint2double(static_cast<int>(h0), static_cast<int>(l0)) +
            __hiloint2double(static_cast<int>(h1), static_cast<int>(l1));
+}
+template <int ROWS>
+__device__ __forceinline__ double add_rows(double v)
+{
+    return add_rows<ROWS>(v, v);
 }
 template <int ROWS>
 __device__ __forceinline__ float add_rows(float v)
@@ -133,15 +140,20 @@ __device__ __forceinline__ float add_rows(float v)
 // a kernel of a few microseconds shows at its end.  (After the step over 8
 // lanes a row repeats itself, so a rotation by 4 meets the lane 4 apart.)
 template <typename T>
-__device__ __forceinline__ T wave_sum(T v)
+__device__ __forceinline__ T row_sum(T v)
 {
-    v = add_rows<32>(v);
-    v = add_rows<16>(v);
     v += dpp<kDppRor8>(v);
     v += dpp<kDppRor4>(v);
     v += dpp<kDppXor2>(v);
     v += dpp<kDppXor1>(v);
     return v;
+}
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v)
+{
+    v = add_rows<32>(v);
+    v = add_rows<16>(v);
+    return row_sum(v);
 }
 
 // Block sums of NV per-thread values in a fixed order (each wave by
@@ -152,11 +164,28 @@ __device__ __forceinline__ void block_partials(const double (&v)[NV], double *__
 {
     constexpr int NW = NT / kWave;
     __shared__ double part[NW][NV];
+    // up to four values share the steps of the butterfly, a row of lanes each
+    // (four values of four waves on a SIMD: 28 additions instead of 96)
+    const int lane = threadIdx.x % kWave, row = lane / 16;
 #pragma unroll
-    for (int u = 0; u < NV; ++u) {
-        const double t = wave_sum(v[u]);
-        if (threadIdx.x % kWave == 0)
-            part[threadIdx.x / kWave][u] = t;
+    for (int u = 0; u < NV; u += 4) {
+        double t;
+        int at = u;  // the value in the lane's row
+        if (NV - u == 1) {
+            t = wave_sum(v[u]);
+        } else if (NV - u == 2) {
+            t = row_sum(add_rows<16>(add_rows<32>(v[u], v[u + 1 < NV ? u + 1 : u])));
+            at += row / 2;
+        } else {
+            const double ab = add_rows<32>(v[u], v[u + 1 < NV ? u + 1 : u]);
+            const double c = v[u + 2 < NV ? u + 2 : u];
+            const double cd = NV - u > 3 ? add_rows<32>(c, v[u + 3 < NV ? u + 3 : u]) : add_rows<32>(c);
+            t = row_sum(add_rows<16>(ab, cd));
+            at += row / 2 + row % 2 * 2;  // rows: a, c, b, d
+        }
+        const bool first = NV - u == 1 ? lane == 0 : NV - u == 2 ? lane % 32 == 0 : lane % 16 == 0;
+        if (first && at < NV)
+            part[threadIdx.x / kWave][at] = t;
     }
     __syncthreads();
     if (threadIdx.x < NV) {

@@ -3,7 +3,7 @@
 // All of them are bound by HBM bandwidth (well under one flop per byte).
 #include <algorithm>
 
-#include "band_f2.h"
+#include "basis_brick.h"
 #include "launch.h"
 #include "march.h"
 #include "opsel.h"
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kBf2Lanes) void k_basis_band(const DevState *__rest
     band_pair<double, true, FIRST, 2, MOM, true>(a, y0, y1, k0, k1, MOM ? mpart + lb : nullptr, mstride);
 }
 
-// Face-coefficient systems that take two steps per launch (FP64): from kBandMin
+// Face-coefficient systems that take two steps per launch in bands (FP64): from kBandMin
 // unknowns, where two single steps begin to cost more than the chain of planes
 // of a pair (2 x 4.1 against 9.1 us at 64^3, 2 x 6.0 against 11.4 at 80^3,
 // 2 x 9.1 against 15.1 at 96^3, 2 x 19.4 against 26.5 at 128^3, 2 x 35 against
@@ -823,15 +823,37 @@ bool band_pairs_apply(const IterArgs &a)
     return 8 * std::max({nz * ny * (nx + 1), nz * (ny + 1) * nx, (nz + 1) * g.nxy}) <= kF2MaxWindow;
 }
 
+// Small 7-point systems that take two steps per launch in bricks
+// (basis_brick.h).  Face coefficients (FP64) from kBrickMin unknowns, below
+// which there is nothing but the launches, to kBrickFaces, where forming half
+// of q twice begins to cost what a launch does (us per two columns, two single
+// steps against a brick: 20^3 5.0 / 4.5, 45^3 6.4 / 5.2, 64^3 8.2 / 7.5, 72^3
+// 10.2 / 11.0); the constant operator, whose other pairs march (basis_f2.h),
+// to kBrickConst (march against brick, FP64: 20^3 8.5 / 3.9, 45^3 8.8 / 4.4,
+// 64^3 9.8 / 5.8, 72^3 10.1 / 8.7, 80^3 10.3 / 10.2; FP32: 45^3 6.3 / 3.5, 72^3
+// 6.8 / 6.5, 80^3 6.8 / 7.6).  Not where the bricks would be mostly empty
+// (thin grids), nor for an odd s, whose last column comes alone with another
+// count of partials.
+constexpr int64_t kBrickMin = 2048, kBrickFaces = 1 << 18, kBrickConst = 3 << 17;
+bool bricks_apply(const IterArgs &a)
+{
+    if (a.s % 2)
+        return false;
+    if (a.op.kind == kOpFaces ? a.fp32 || a.op.n < kBrickMin || a.op.n > kBrickFaces
+                              : a.op.kind != kOpPoisson || a.op.n > kBrickConst)
+        return false;
+    return static_cast<int64_t>(plan_brick(a.op.g).nbl) * kBrick * kBrick * kBrick <= 4 * a.op.n;
+}
+
 // The two-step kernels serve the Chebyshev basis of the constant operators and
-// of large face-coefficient systems when AP is not stored (moments, recurrence
-// and operator-applying Gram kinds).
+// of face-coefficient systems when AP is not stored (moments, recurrence and
+// operator-applying Gram kinds).
 bool basis_pairs_apply(const IterArgs &a)
 {
     if (a.AP || a.monomial || a.one_step)
         return false;
     if (a.op.kind == kOpFaces)
-        return band_pairs_apply(a);
+        return bricks_apply(a) || band_pairs_apply(a);
     if (a.op.kind != kOpPoisson && a.op.kind != kOpPoisson27)
         return false;
     if (a.op.kind == kOpPoisson27 && a.op.n < kF2BoxMin)
@@ -882,9 +904,47 @@ hipError_t basis_band_v(const IterArgs &a, int j, hipStream_t st)
     return hipGetLastError();
 }
 
+template <typename T, bool FACES, bool MOM>
+hipError_t basis_brick_v(const IterArgs &a, int j, hipStream_t st)
+{
+    const BrickPlan plan = plan_brick(a.op.g);
+    T *pj = static_cast<T *>(a.P) + j * a.ld;
+    BandArgs<T> b{a.op.g.nx, a.op.g.ny, a.op.g.nz, a.op.precond, static_cast<T>(a.theta), static_cast<T>(a.sigma),
+                  nullptr, nullptr, nullptr, pj, pj - (j > 0 ? a.ld : 0), pj + a.ld, pj + 2 * a.ld};
+    if constexpr (FACES)
+        b.kx = a.op.kx, b.ky = a.op.ky, b.kz = a.op.kz;
+    double *mp = MOM ? a.mpart + static_cast<int64_t>(mom_slot(j)) * a.mstride : nullptr;
+    const dim3 grid(plan.per * kNumXcd), block(kBrickThreads);
+    const StopArgs stop{a.rpart, a.dbg + dbg_rho(a.s), a.hist, a.nbr, a.hist_cap};
+    if (j > 0)
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, false, MOM, false>), grid, block, 0, st, a.st, b, plan, mp,
+                           a.mstride, stop);
+    else if (MOM && a.small)
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, MOM>), grid, block, 0, st, a.st, b, plan, mp,
+                           a.mstride, stop);
+    else
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, false>), grid, block, 0, st, a.st, b, plan, mp,
+                           a.mstride, stop);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t basis_brick(const IterArgs &a, int j, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 8) {  // the moments kind and the faces are FP64 only
+        if (a.op.kind == kOpFaces)
+            return a.gram_mom ? basis_brick_v<T, true, true>(a, j, st) : basis_brick_v<T, true, false>(a, j, st);
+        if (a.gram_mom)
+            return basis_brick_v<T, false, true>(a, j, st);
+    }
+    return basis_brick_v<T, false, false>(a, j, st);
+}
+
 template <typename T>
 hipError_t basis_pair(const IterArgs &a, int j, hipStream_t st)
 {
+    if (bricks_apply(a))
+        return basis_brick<T>(a, j, st);
     if (a.op.kind == kOpFaces)
         return a.gram_mom ? basis_band_v<true>(a, j, st) : basis_band_v<false>(a, j, st);
     if constexpr (sizeof(T) == 8)  // the moments kind is FP64 only
@@ -1160,7 +1220,8 @@ int basis_kernel_count(const IterArgs &a, int *pairs)
 
 bool small_chain(const IterArgs &a)
 {
-    return a.gram_mom && a.op.n <= kSmallMax && !basis_pairs_apply(a) && !march_step(a.op, 8);
+    return a.gram_mom && a.op.n <= kSmallMax &&
+           (basis_pairs_apply(a) ? bricks_apply(a) : !march_step(a.op, 8));
 }
 
 hipError_t launch_basis_all(const IterArgs &a, hipStream_t st)
@@ -1193,7 +1254,9 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
     };
     int j = 0;
     if (basis_pairs_apply(a)) {
-        const int64_t nbl = a.op.kind == kOpFaces ? plan_bands(a.op.g).nbl : f2_plan(a).nbl;
+        const int64_t nbl = bricks_apply(a)          ? plan_brick(a.op.g).nbl
+                            : a.op.kind == kOpFaces ? plan_bands(a.op.g).nbl
+                                                    : f2_plan(a).nbl;
         for (; j + 2 <= m; j += 2)
             put(j, 2, nbl);
     }

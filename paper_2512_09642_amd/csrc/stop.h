@@ -3,7 +3,7 @@
 // residual kernel and before any basis or Gram work of iteration k.
 #pragma once
 
-#include "common.h"
+#include "launch.h"
 
 namespace sstep {
 
