@@ -290,14 +290,15 @@ int32_t sstep_gram_mode(const sstep_ctx *ctx);
 /* Kernel launches that form the basis p_1 .. p_m of one outer iteration
  * (Sec. 2, Definition; m = s - 1 with SSTEP_GRAM_APPLY_OP, else s).  With
  * basis_steps = 0, for the constant 7-point operator (any size) and the
- * 27-point operator (327680 unknowns or more) with the Chebyshev basis and AP
- * not stored, for the 7-point face-coefficient operator in FP64 (the same
+ * 27-point operator (327680 unknowns or more, not in grids of one plane or of
+ * rows and columns too short to fill its tiles) with the Chebyshev basis and
+ * AP not stored, for the 7-point face-coefficient operator in FP64 (the same
  * conditions) with 524288 unknowns or more and rows of at most 256 points, or
- * 2048 to 262144 unknowns and even s (not in grids so thin that their 8 x 8 x
- * 8 bricks are mostly empty), and for batched stencil systems with the recurrence Gram kind, one launch forms
- * two consecutive columns (p_{j+1} and p_{j+2} from p_{j-1} and p_j, exactly
- * as two single steps would; a single face-coefficient system's up to the
- * rounding of the operator), and *pairs (if pairs
+ * with 2048 to 262144 unknowns and even s, and for batched stencil systems
+ * with the recurrence Gram kind, one launch forms two consecutive columns
+ * (p_{j+1} and p_{j+2} from p_{j-1} and p_j, exactly as two single steps
+ * would; a single face-coefficient system's up to the rounding of the
+ * operator), and *pairs (if pairs
  * is not NULL) receives how many launches do so; an odd m ends with a single
  * step.  Otherwise every launch forms one column and *pairs is 0.  A batched
  * context takes two steps per launch only when every system's grid row fits
@@ -310,8 +311,7 @@ int32_t sstep_basis_launches(const sstep_ctx *ctx, int32_t *pairs);
  * lmin[q] < lmax[q] (host arrays).  The outer iteration of every
  * (system, rhs) pair advances together: each step of it (residual, stopping
  * test, the basis steps, Gram, FGS, update) is one launch over all pairs, at
- * most s + 5
- * launches per outer iteration (fewer when basis launches form two columns,
+ * most s + 5 launches per outer iteration (fewer when basis launches form two columns,
  * see sstep_basis_launches), graph_chunk outer iterations per graph replay; a
  * pair that has stopped is skipped by every launch. */
 sstep_status sstep_setup_batched(sstep_ctx **out, int32_t nsys, const sstep_operator *A, int32_t nrhs, int32_t s,

@@ -2067,9 +2067,12 @@ sstep_status sstep_coarse_info(const sstep_ctx *ctx, int64_t *n_coarse, int64_t 
 namespace {
 
 constexpr size_t kNoallocBytes = size_t(64) << 20;
+// Room beside it for the residual's partials, so that the limit on the problem
+// does not move with the kernel that forms them (noalloc_counted).
+constexpr size_t kNoallocPartials = size_t(16) << 10;
 constexpr int kNoallocMaxDevices = 64;
 
-__device__ __align__(256) char scratch[kNoallocBytes];
+__device__ __align__(256) char scratch[kNoallocBytes + kNoallocPartials];
 
 std::mutex g_noalloc_mutex;
 void *g_noalloc_ptr[kNoallocMaxDevices] = {};
@@ -2099,7 +2102,21 @@ sstep_status noalloc_scratch(char **out)
 // Byte offsets of the workspace regions in the scratch array, 256-aligned.
 struct NoallocLayout {
     size_t st, rpart, gpart, gsum, dbg, hist, bad, dvec, invd, P, AP, total;
+    size_t counted;  // what the limit is held against
 };
+
+// Partials of the residual that the limit counts: blocks of 1024 threads of 2
+// x-points and 8 planes for the constant 7-point operator with an even
+// x-extent, when at most 1024, else one per 256 rows, at most 1024.
+int64_t noalloc_counted(const OpDev &op)
+{
+    if (op.kind == kOpPoisson && op.g.nx % 2 == 0) {
+        const int64_t blocks = ((op.g.nxy / 2 + 1023) / 1024) * ((op.g.nz + 7) / 8);
+        if (blocks <= 1024)
+            return blocks;
+    }
+    return std::min<int64_t>(1024, (op.n + kBlock - 1) / kBlock);
+}
 
 NoallocLayout noalloc_layout(const IterArgs &it)
 {
@@ -2125,6 +2142,8 @@ NoallocLayout noalloc_layout(const IterArgs &it)
     L.P = take(ld * size_t(it.s + it.gram_rec) * sizeof(double));
     L.AP = take(it.gram_op || it.gram_rec ? 0 : ld * size_t(it.s) * sizeof(double));
     L.total = o;
+    take(size_t(noalloc_counted(it.op)) * sizeof(double));
+    L.counted = o - (L.gpart - L.rpart);
     return L;
 }
 
@@ -2201,10 +2220,15 @@ sstep_status noalloc_impl(const sstep_operator *A, int32_t s, int32_t nu, double
     it.hist_cap = 0;
     set_residual_schedule(it);
     set_gram_schedule(it, default_gram_schedule(it));  // the context path's schedule without autotuning
+    if (size_t(it.nbr) * sizeof(double) > kNoallocPartials) {  // a march of many thin ranges: row chunks instead
+        it.res_m = 0;
+        it.nbr = 1024;
+        it.rchunk = round_up((op.n + it.nbr - 1) / it.nbr, kBlock);
+    }
     const NoallocLayout L = noalloc_layout(it);
-    if (L.total > kNoallocBytes)
+    if (L.counted > kNoallocBytes)
         return fail(nullptr, SSTEP_E_ARG,
-                    "problem too large for the allocation-free solve: needs " + std::to_string(L.total) +
+                    "problem too large for the allocation-free solve: needs " + std::to_string(L.counted) +
                         " bytes of workspace, the static scratch holds " + std::to_string(kNoallocBytes));
 
     char *base = nullptr;

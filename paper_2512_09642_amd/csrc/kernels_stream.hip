@@ -542,9 +542,24 @@ constexpr int64_t kMarchResidual = 5 * (int64_t(1) << 16);
 // 25.9 / 67 against 15.9 / 23.1 / 47.5, FP32 the same at 160^3 and 224^3.
 constexpr int64_t kMarchStep27 = int64_t(4) << 20, kMarchStep7 = int64_t(24) << 20;
 
+// Grids that leave more than 9 of 11 lanes of their 64 x 32 tiles idle, or of
+// one plane: there the marched kernels give way to a thread per point (the
+// 7-point pairs to bricks).  us, marched against not, FP64: 16 x 16 x 4096
+// residual 20.5 / 11.1, pair of 7-point steps 25 / 18, 27-point residual and
+// basis (s = 16) 285 / 294; 8 x 300 x 300 17.6 / 9.3, 23 / 12, 269 / 235; 1 x
+// 1000 x 1000 103 / 9.8, 163 / 12, 1577 / 151; 2048 x 2048 x 1 42 / 28, 85 /
+// 40, 938 / 511; and above the line 20 x 20 x 1500 7-point pair 14.3, 27-point
+// 178 / 234, 1024 x 1024 x 2 25 and 339 / 431.
+bool thin(const Grid3 &g)
+{
+    const F2Plan p = plan_march(g, false, 8);
+    const int64_t lanes = static_cast<int64_t>(p.tiles_x) * p.tiles_y * kF2Lanes * kF2Ext;
+    return g.nz < 2 || 11 * g.nxy < 2 * lanes;
+}
+
 bool march_fits(const OpDev &op, int elem)
 {
-    return (op.kind == kOpPoisson || op.kind == kOpPoisson27) &&
+    return (op.kind == kOpPoisson || op.kind == kOpPoisson27) && !thin(op.g) &&
            f2_window_bytes(op.g, plan_march(op.g, op.kind == kOpPoisson27, elem).kz, elem) <= kF2MaxWindow;
 }
 
@@ -831,18 +846,16 @@ bool band_pairs_apply(const IterArgs &a)
 // 10.2 / 11.0); the constant operator, whose other pairs march (basis_f2.h),
 // to kBrickConst (march against brick, FP64: 20^3 8.5 / 3.9, 45^3 8.8 / 4.4,
 // 64^3 9.8 / 5.8, 72^3 10.1 / 8.7, 80^3 10.3 / 10.2; FP32: 45^3 6.3 / 3.5, 72^3
-// 6.8 / 6.5, 80^3 6.8 / 7.6).  Not where the bricks would be mostly empty
-// (thin grids), nor for an odd s, whose last column comes alone with another
-// count of partials.
+// 6.8 / 6.5, 80^3 6.8 / 7.6).  With face
+// coefficients not for an odd s, whose last column comes alone with another
+// count of partials; the constant operator takes two columns at any s, and
+// bricks in thin grids of any size (thin, above).
 constexpr int64_t kBrickMin = 2048, kBrickFaces = 1 << 18, kBrickConst = 3 << 17;
 bool bricks_apply(const IterArgs &a)
 {
-    if (a.s % 2)
-        return false;
-    if (a.op.kind == kOpFaces ? a.fp32 || a.op.n < kBrickMin || a.op.n > kBrickFaces
-                              : a.op.kind != kOpPoisson || a.op.n > kBrickConst)
-        return false;
-    return static_cast<int64_t>(plan_brick(a.op.g).nbl) * kBrick * kBrick * kBrick <= 4 * a.op.n;
+    if (a.op.kind == kOpFaces)
+        return !a.fp32 && a.s % 2 == 0 && a.op.n >= kBrickMin && a.op.n <= kBrickFaces;
+    return a.op.kind == kOpPoisson && (a.op.n <= kBrickConst || thin(a.op.g));
 }
 
 // The two-step kernels serve the Chebyshev basis of the constant operators and
@@ -856,7 +869,9 @@ bool basis_pairs_apply(const IterArgs &a)
         return bricks_apply(a) || band_pairs_apply(a);
     if (a.op.kind != kOpPoisson && a.op.kind != kOpPoisson27)
         return false;
-    if (a.op.kind == kOpPoisson27 && a.op.n < kF2BoxMin)
+    if (bricks_apply(a))
+        return true;
+    if (a.op.kind == kOpPoisson27 && (a.op.n < kF2BoxMin || thin(a.op.g)))
         return false;
     return f2_window_bytes(a.op.g, f2_plan(a).kz, a.fp32 ? 4 : 8) <= kF2MaxWindow;
 }
@@ -904,10 +919,9 @@ hipError_t basis_band_v(const IterArgs &a, int j, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, bool FACES, bool MOM>
-hipError_t basis_brick_v(const IterArgs &a, int j, hipStream_t st)
+template <typename T, bool FACES, bool MOM, bool CUBE>
+hipError_t basis_brick_v(const IterArgs &a, int j, const BrickPlan &plan, hipStream_t st)
 {
-    const BrickPlan plan = plan_brick(a.op.g);
     T *pj = static_cast<T *>(a.P) + j * a.ld;
     BandArgs<T> b{a.op.g.nx, a.op.g.ny, a.op.g.nz, a.op.precond, static_cast<T>(a.theta), static_cast<T>(a.sigma),
                   nullptr, nullptr, nullptr, pj, pj - (j > 0 ? a.ld : 0), pj + a.ld, pj + 2 * a.ld};
@@ -917,15 +931,23 @@ hipError_t basis_brick_v(const IterArgs &a, int j, hipStream_t st)
     const dim3 grid(plan.per * kNumXcd), block(kBrickThreads);
     const StopArgs stop{a.rpart, a.dbg + dbg_rho(a.s), a.hist, a.nbr, a.hist_cap};
     if (j > 0)
-        hipLaunchKernelGGL((k_basis_brick<T, FACES, false, MOM, false>), grid, block, 0, st, a.st, b, plan, mp,
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, false, MOM, false, CUBE>), grid, block, 0, st, a.st, b, plan, mp,
                            a.mstride, stop);
     else if (MOM && a.small)
-        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, MOM>), grid, block, 0, st, a.st, b, plan, mp,
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, MOM, CUBE>), grid, block, 0, st, a.st, b, plan, mp,
                            a.mstride, stop);
     else
-        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, false>), grid, block, 0, st, a.st, b, plan, mp,
+        hipLaunchKernelGGL((k_basis_brick<T, FACES, true, MOM, false, CUBE>), grid, block, 0, st, a.st, b, plan, mp,
                            a.mstride, stop);
     return hipGetLastError();
+}
+
+template <typename T, bool FACES, bool MOM>
+hipError_t basis_brick_shape(const IterArgs &a, int j, hipStream_t st)
+{
+    const BrickPlan plan = plan_brick(a.op.g);
+    return plan.cube() ? basis_brick_v<T, FACES, MOM, true>(a, j, plan, st)
+                       : basis_brick_v<T, FACES, MOM, false>(a, j, plan, st);
 }
 
 template <typename T>
@@ -933,11 +955,11 @@ hipError_t basis_brick(const IterArgs &a, int j, hipStream_t st)
 {
     if constexpr (sizeof(T) == 8) {  // the moments kind and the faces are FP64 only
         if (a.op.kind == kOpFaces)
-            return a.gram_mom ? basis_brick_v<T, true, true>(a, j, st) : basis_brick_v<T, true, false>(a, j, st);
+            return a.gram_mom ? basis_brick_shape<T, true, true>(a, j, st) : basis_brick_shape<T, true, false>(a, j, st);
         if (a.gram_mom)
-            return basis_brick_v<T, false, true>(a, j, st);
+            return basis_brick_shape<T, false, true>(a, j, st);
     }
-    return basis_brick_v<T, false, false>(a, j, st);
+    return basis_brick_shape<T, false, false>(a, j, st);
 }
 
 template <typename T>
@@ -1221,7 +1243,7 @@ int basis_kernel_count(const IterArgs &a, int *pairs)
 bool small_chain(const IterArgs &a)
 {
     return a.gram_mom && a.op.n <= kSmallMax &&
-           (basis_pairs_apply(a) ? bricks_apply(a) : !march_step(a.op, 8));
+           (basis_pairs_apply(a) ? bricks_apply(a) && a.s % 2 == 0 : !march_step(a.op, 8));
 }
 
 hipError_t launch_basis_all(const IterArgs &a, hipStream_t st)

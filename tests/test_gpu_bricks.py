@@ -1,7 +1,8 @@
 """Two basis steps per launch of a small 7-point system in bricks of 8^3
 points: grids that fill the bricks, leave one plane, row or column over, or
 end inside one; both sides of the rule's lines (2048 and 2^18 unknowns with
-face coefficients, 3 2^17 with the constant operator, thin grids, odd s); the
+face coefficients, 3 2^17 with the constant operator, odd s); thin grids of
+every orientation, whose bricks span one or two axes; the
 moments kind with the stopping test in the first launch (to 131072 unknowns)
 and without, the recurrence kind, no Jacobi, FP32+IR.  Two lockstep iterations
 against the oracle (1e-10; 1e-4 for the FP32 Gram matrix), and, where the pairs
@@ -21,7 +22,10 @@ pytestmark = pytest.mark.gpu
 CASES = [("faces", (16, 16, 8), 4, {}, 2), ("faces", (17, 9, 15), 6, {}, 3), ("faces", (16, 16, 7), 4, {}, 0),
          ("faces", (24, 23, 25), 5, {}, 0), ("faces", (13, 14, 15), 2, dict(precond=False), 1),
          ("faces", (64, 64, 64), 4, {}, 2), ("faces", (65, 64, 64), 4, {}, 0), ("faces", (50, 51, 52), 4, {}, 2),
-         ("faces", (128, 9, 9), 4, dict(gram="recurrence"), 2), ("faces", (512, 2, 4), 4, {}, 0),
+         ("faces", (128, 9, 9), 4, dict(gram="recurrence"), 2), ("faces", (512, 2, 4), 4, {}, 2), ("faces", (1, 3000, 1), 4, {}, 2),
+         ("const", (1, 1000, 500), 4, {}, 2), ("const", (500001, 1, 1), 5, {}, 2), ("const", (3, 3, 60000), 4, {}, 2),
+         ("const", (900, 600, 1), 2, {}, 1), ("const", (2, 1, 1), 1, {}, 0), ("const", (1, 1, 3), 2, {}, 1),
+         ("const", (17, 1030, 2), 3, dict(precond=False), 1),
          ("const", (8, 8, 8), 8, {}, 4), ("const", (5, 4, 3), 4, {}, 2), ("const", (9, 9, 9), 16, {}, 8),
          ("const", (31, 16, 33), 4, dict(precond=False), 2), ("const", (72, 73, 74), 4, {}, 2),
          ("const", (64, 96, 64), 4, {}, 2), ("const", (20, 21, 22), 6, dict(gram="apply"), 2)]
