@@ -293,8 +293,9 @@ int32_t sstep_gram_mode(const sstep_ctx *ctx);
  * 27-point operator (327680 unknowns or more, not in grids of one plane or of
  * rows and columns too short to fill its tiles) with the Chebyshev basis and
  * AP not stored, for the 7-point face-coefficient operator in FP64 (the same
- * conditions) with 524288 unknowns or more and rows of at most 256 points, or
- * with 2048 to 262144 unknowns and even s, and for batched stencil systems
+ * conditions) with 524288 unknowns or more in grids that its bands of whole
+ * rows suit (no rows above 341 points, no few planes), or with 2048 to 262144
+ * unknowns and even s, and for batched stencil systems
  * with the recurrence Gram kind, one launch forms two consecutive columns
  * (p_{j+1} and p_{j+2} from p_{j-1} and p_j, exactly as two single steps
  * would; a single face-coefficient system's up to the rounding of the

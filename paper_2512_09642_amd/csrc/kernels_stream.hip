@@ -779,6 +779,8 @@ struct BandPlan {
     int h, kz;  // rows of a band, planes of a range
     uint32_t bands, ranges, nbl, per;
 };
+// Plane steps of the busiest CU: two of the halo and about two to start.
+int64_t band_steps(int64_t nbl, int kz) { return (nbl + kF2Cus - 1) / kF2Cus * (kz + 2 + 2); }
 BandPlan plan_bands(const Grid3 &g)
 {
     BandPlan p{};
@@ -791,7 +793,7 @@ BandPlan plan_bands(const Grid3 &g)
     int64_t best = INT64_MAX;
     for (int kz = 1; kz <= kBf2MaxPlanes && kz <= g.nz; ++kz) {
         const int64_t nbl = static_cast<int64_t>(p.bands) * ((g.nz + kz - 1) / kz);
-        const int64_t cost = (nbl + kF2Cus - 1) / kF2Cus * (kz + 2 + 2);
+        const int64_t cost = band_steps(nbl, kz);
         if (cost < best)
             best = cost, p.kz = kz;
     }
@@ -818,21 +820,26 @@ __global__ __launch_bounds__(kBf2Lanes) void k_basis_band(const DevState *__rest
     band_pair<double, true, FIRST, 2, MOM, true>(a, y0, y1, k0, k1, MOM ? mpart + lb : nullptr, mstride);
 }
 
-// Face-coefficient systems that take two steps per launch in bands (FP64): from kBandMin
-// unknowns, where two single steps begin to cost more than the chain of planes
-// of a pair (2 x 4.1 against 9.1 us at 64^3, 2 x 6.0 against 11.4 at 80^3,
-// 2 x 9.1 against 15.1 at 96^3, 2 x 19.4 against 26.5 at 128^3, 2 x 35 against
-// 50 at 160^3), and with rows of at most kBandRow points, four to a block, two
-// of them its own (2 x 34.5 against 58 us at 256 x 256 x 60, but 2 x 44
-// against 109 at 341 x 341 x 40, one row of three).  Stored through the
-// caches, which hold the columns of such a system for the next launch (128^3:
-// 30.0 us past them, 27.5 through).
-constexpr int64_t kBandMin = int64_t(1) << 19;
-constexpr int kBandRow = kBf2Threads / 4;
+// Face-coefficient systems that take two steps per launch in bands (FP64), from
+// kBandMin unknowns, where two single steps begin to cost more than the chain
+// of planes of a pair (2 x 4.1 against 9.1 us at 64^3, 2 x 6.0 against 11.4 at
+// 80^3, 2 x 9.1 against 15.1 at 96^3, 2 x 19.4 against 26.5 at 128^3, 2 x 35
+// against 50 at 160^3), and where the bands suit the grid: a pair takes about
+// 1.6 us a plane step of the busiest CU, a single step 1.6 us and 8.5 a million
+// unknowns, so a pair pays below two steps and one per kBandStep unknowns (256
+// x 64 x 64: 19.4 against 2 x 10.4 us, 12 steps; 200 x 3000 x 1: 26.2 against
+// 2 x 6.3, 20 steps; 16 x 16 x 4096: 26.0 against 2 x 10.1, 20; 341 x 341 x 40:
+// 109 against 2 x 44, 88).  Stored through the caches, which hold the columns
+// of such a system for the next launch (128^3: 30.0 us past them, 27.5
+// through).
+constexpr int64_t kBandMin = int64_t(1) << 19, kBandStep = 94000;
 bool band_pairs_apply(const IterArgs &a)
 {
     const Grid3 &g = a.op.g;
-    if (a.op.kind != kOpFaces || a.fp32 || a.op.n < kBandMin || g.nx > kBandRow)
+    if (a.op.kind != kOpFaces || a.fp32 || a.op.n < kBandMin)
+        return false;
+    const BandPlan p = plan_bands(g);
+    if (!p.bands || (band_steps(p.nbl, p.kz) - 2) * kBandStep >= a.op.n)
         return false;
     const int64_t nx = g.nx, ny = g.ny, nz = g.nz;
     return 8 * std::max({nz * ny * (nx + 1), nz * (ny + 1) * nx, (nz + 1) * g.nxy}) <= kF2MaxWindow;
