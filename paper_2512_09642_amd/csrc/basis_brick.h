@@ -9,8 +9,8 @@
 //
 // What bounds it: the launch and one chain of loads, as a single step's, paid
 // once for two columns; half of q is formed twice, which costs little while
-// the chip is not filled (45^3, s = 16, face coefficients: 5.2 us for two
-// columns, 6.4 in single steps; constant operator 4.4, 8.8 by the march).
+// the chip is not filled (45^3, s = 16, face coefficients: 5.4 us for two
+// columns, 6.4 in single steps; constant operator 4.6, 8.8 by the march).
 #pragma once
 
 #include "band_f2.h"

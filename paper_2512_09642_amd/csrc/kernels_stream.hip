@@ -536,6 +536,10 @@ hipError_t residual_for(const IterArgs &a, const Op &op, hipStream_t st, bool wr
 // 64^3 / 96^3 / 224^3: 27-point 9.3 / 23.6 / 288 us one point per thread
 // against 10.1 / 15.4 / 53 marched; 7-point 8.3 / 13.1 / 49.6 marched.
 constexpr int64_t kMarchResidual = 5 * (int64_t(1) << 16);
+// The residual's march wants a third of its lanes (us, marched against a thread
+// per point, 7-point FP64: 20 x 20 x 1500 14.6 / 9.2, 32 x 32 x 600 14.4 / 9.6, 300
+// x 8 x 300 14.6 / 9.3; 27-point equal; and above the line 300 x 300 x 8 8.7).
+constexpr double kMarchResidualFill = 1.0 / 3.0;
 // One basis step, by the bytes of a vector: 27-point FP64 64^3 / 96^3 / 224^3
 // 6.9 / 17.4 / 162 us against 8.6 / 12.4 / 52, FP32 96^3 / 128^3 8.0 / 16.9
 // against 8.6 / 11.2; 7-point FP64 with products 128^3 / 160^3 / 224^3 15.2 /
@@ -550,11 +554,11 @@ constexpr int64_t kMarchStep27 = int64_t(4) << 20, kMarchStep7 = int64_t(24) << 
 // 1000 x 1000 103 / 9.8, 163 / 12, 1577 / 151; 2048 x 2048 x 1 42 / 28, 85 /
 // 40, 938 / 511; and above the line 20 x 20 x 1500 7-point pair 14.3, 27-point
 // 178 / 234, 1024 x 1024 x 2 25 and 339 / 431.
-bool thin(const Grid3 &g)
+bool thin(const Grid3 &g, double fill = 2.0 / 11.0)
 {
     const F2Plan p = plan_march(g, false, 8);
     const int64_t lanes = static_cast<int64_t>(p.tiles_x) * p.tiles_y * kF2Lanes * kF2Ext;
-    return g.nz < 2 || 11 * g.nxy < 2 * lanes;
+    return g.nz < 2 || static_cast<double>(g.nxy) < fill * static_cast<double>(lanes);
 }
 
 bool march_fits(const OpDev &op, int elem)
@@ -849,10 +853,10 @@ bool band_pairs_apply(const IterArgs &a)
 // (basis_brick.h).  Face coefficients (FP64) from kBrickMin unknowns, below
 // which there is nothing but the launches, to kBrickFaces, where forming half
 // of q twice begins to cost what a launch does (us per two columns, two single
-// steps against a brick: 20^3 5.0 / 4.5, 45^3 6.4 / 5.2, 64^3 8.2 / 7.5, 72^3
+// steps against a brick: 20^3 5.0 / 4.8, 45^3 6.4 / 5.4, 64^3 8.2 / 7.7, 72^3
 // 10.2 / 11.0); the constant operator, whose other pairs march (basis_f2.h),
-// to kBrickConst (march against brick, FP64: 20^3 8.5 / 3.9, 45^3 8.8 / 4.4,
-// 64^3 9.8 / 5.8, 72^3 10.1 / 8.7, 80^3 10.3 / 10.2; FP32: 45^3 6.3 / 3.5, 72^3
+// to kBrickConst (march against brick, FP64: 20^3 8.5 / 4.1, 45^3 8.8 / 4.6,
+// 64^3 9.8 / 5.9, 72^3 10.1 / 8.7, 80^3 10.3 / 10.2; FP32: 45^3 6.3 / 3.5, 72^3
 // 6.8 / 6.5, 80^3 6.8 / 7.6).  With face
 // coefficients not for an odd s, whose last column comes alone with another
 // count of partials; the constant operator takes two columns at any s, and
@@ -1197,7 +1201,7 @@ int residual_threads(int64_t n) { return point_threads(n); }
 
 int residual_march_blocks(const OpDev &op)
 {
-    return op.n >= kMarchResidual && march_fits(op, 8)
+    return op.n >= kMarchResidual && march_fits(op, 8) && !thin(op.g, kMarchResidualFill)
                ? static_cast<int>(plan_march(op.g, op.kind == kOpPoisson27, 8).nbl)
                : 0;
 }
