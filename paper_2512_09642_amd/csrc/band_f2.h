@@ -156,6 +156,10 @@ __device__ __forceinline__ void band_pair(const BandArgs<T> &a, int y0, int y1, 
         ps[tid & 1][z] = T(0);
         qs[tid & 1][z] = T(0);
     }
+    // The first plane step reads the other plane of q before any was stored: what
+    // it forms is not stored, but its products are summed with weight 0, and what
+    // an earlier block left in the LDS may be NaN.
+    qs[1][kBf2Front + 2 * tid] = qs[1][kBf2Front + 2 * tid + 1] = T(0);
     // rows of the block: the band and the row on each side of it
     const int ye0 = y0 > 0 ? y0 - 1 : 0;
     const int ye1 = y1 < ny ? y1 + 1 : ny;
