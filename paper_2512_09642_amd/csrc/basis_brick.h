@@ -71,14 +71,18 @@ __global__ __launch_bounds__(kBrickThreads) void k_basis_brick(DevState *__restr
                                                                int64_t mstride, StopArgs stop)
 {
     __shared__ T qs[kBrickThreads];
-    if (st->done)
+    // with the test in this launch the flag may be set as the block starts: the
+    // block leaves at the test's barrier
+    const int done = wave_done(st);
+    if (!STOP && done)
         return;
     const uint32_t lb = xcd_block(blockIdx.x, plan.per);
     if (lb >= plan.nbl)
         return;  // whole block
     double share = 0.0;
     if constexpr (STOP)
-        share = partial_share<kBrickThreads>(stop);
+        if (!done)
+            share = partial_share<kBrickThreads>(stop);
     const uint32_t cxy = static_cast<uint32_t>(plan.x.cnt) * plan.y.cnt;
     const int bz = static_cast<int>(lb / cxy), bxy = static_cast<int>(lb - bz * cxy);
     const int by = bxy / plan.x.cnt, bx = bxy - by * plan.x.cnt;
@@ -97,7 +101,7 @@ __global__ __launch_bounds__(kBrickThreads) void k_basis_brick(DevState *__restr
     const T two_theta = T(2) * a.theta;
     T pc = T(0), q = T(0), dinv = a.precond ? T(1) / T(6) : T(1), d = T(1);
     T fw = T(0), fe = T(0), fs = T(0), fn = T(0), fb = T(0), ft = T(0);
-    if (dom) {
+    if (dom && !done) {
         const T *__restrict__ p = a.pj;
         pc = p[c];
         const T w = i > 0 ? p[c - 1] : T(0), e = i + 1 < nx ? p[c + 1] : T(0);
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(kBrickThreads) void k_basis_brick(DevState *__restr
     }
     qs[tid] = q;  // 0 off the grid
     if constexpr (STOP)
-        if (stop_at_head<kBrickThreads>(st, stop, share, lb == 0))
+        if (stop_at_head<kBrickThreads>(st, done, stop, share, lb == 0))
             return;
     __syncthreads();
     double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0, m4 = 0.0;

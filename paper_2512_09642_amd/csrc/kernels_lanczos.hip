@@ -114,9 +114,16 @@ __global__ __launch_bounds__(kBlock) void k_lz_apply(LzState *__restrict__ ls, c
                                                      Op op)
 {
     const uint32_t lb = xcd_block(blockIdx.x, per);
-    if (ls->stopped || lb >= static_cast<uint32_t>(cnt))
+    if (lb >= static_cast<uint32_t>(cnt))
         return;  // whole block
+    // the first block may end the recurrence as this one starts: one thread
+    // reads the flag, and the barrier of the sum hands it to all
+    __shared__ int ended;
+    if (threadIdx.x == 0)
+        ended = ls->stopped;
     const double scale = sqrt(sum_partials(pin, cnt));
+    if (ended)
+        return;
     // j = 0: amax = 0, a zero or non-finite start
     const bool stop = beta_stops(scale, ls->amax);
     if (lb == 0 && threadIdx.x == 0) {

@@ -156,26 +156,30 @@ __global__ __launch_bounds__(NT) void k_basis_mom(DevState *__restrict__ st, con
                                                       Op op)
 {
     static_assert(STEP == 0 || STEP == 1, "the moments kind forms every column");
-    if (st->done)
+    // with the test in this launch the flag may be set as the block starts: a
+    // block of several waves leaves at the test's barrier, not here
+    const int done = wave_done(st);
+    if (done && !(STOP && NT > kWave))
         return;
     const uint32_t lb = xcd_block(blockIdx.x, per);
     if (lb >= nbl)
         return;  // whole block
-    double share = 0.0;
-    if constexpr (STOP)
-        share = partial_share<NT>(stop);
     const int64_t c = static_cast<int64_t>(lb) * NT + threadIdx.x;
     const bool valid = c < n;
     const int64_t cc = valid ? c : n - 1;
-    T pc, y, dinv, wt;
-    op.apply_w(pj, cc, pc, y, dinv, wt);
-    T pn;
-    if constexpr (STEP == 0)
-        pn = theta * (dinv * y - sigma * pc);
-    else
-        pn = T(2) * theta * (dinv * y - sigma * pc) - __builtin_nontemporal_load(pprev + cc);
+    double share = 0.0;
+    T pc = T(0), y = T(0), dinv = T(0), wt = T(0), pn = T(0);
+    if (!done) {
+        if constexpr (STOP)
+            share = partial_share<NT>(stop);
+        op.apply_w(pj, cc, pc, y, dinv, wt);
+        if constexpr (STEP == 0)
+            pn = theta * (dinv * y - sigma * pc);
+        else
+            pn = T(2) * theta * (dinv * y - sigma * pc) - __builtin_nontemporal_load(pprev + cc);
+    }
     if constexpr (STOP)
-        if (stop_at_head<NT>(st, stop, share, lb == 0))
+        if (stop_at_head<NT>(st, done, stop, share, lb == 0))
             return;
     if (valid)
         pnext[c] = pn;

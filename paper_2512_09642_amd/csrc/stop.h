@@ -104,13 +104,19 @@ __device__ inline double fixed_order_sum(const double *part, int cnt)
 // of its own: every block sums the partials in the same order and decides for
 // itself; the block that record names writes the state.  The others read only
 // what no test of this solve changes after the first residual, which is told
-// by the iteration count.  part_sum: the thread's share of the partials
-// (partial_share).  Every thread of the block must call it.
+// by the iteration count, and st->done, which may be set while they start: done
+// is what each wave read, and a block stops as a whole when any of its waves
+// read it set (the recording block then takes the same decision).  part_sum: the
+// thread's share of the partials (partial_share), of no meaning in a wave whose
+// done is set.  Every thread of the block must call it; it returns the same to
+// all of them.
 struct StopArgs {
     const double *rpart;
     double *dbg_rho, *hist;
     int nbr, hist_cap;
 };
+// st->done as one value for the wave.
+__device__ __forceinline__ int wave_done(const DevState *st) { return __builtin_amdgcn_readfirstlane(st->done); }
 template <int NT>
 __device__ __forceinline__ double partial_share(const StopArgs &a)
 {
@@ -120,18 +126,25 @@ __device__ __forceinline__ double partial_share(const StopArgs &a)
     return acc;
 }
 template <int NT>
-__device__ __forceinline__ int stop_at_head(DevState *st, const StopArgs &a, double part_sum, bool record)
+__device__ __forceinline__ int stop_at_head(DevState *st, int done, const StopArgs &a, double part_sum, bool record)
 {
     double rho2 = wave_sum(part_sum);
     if constexpr (NT > kWave) {
         __shared__ double wsum[NT / kWave];
-        if (threadIdx.x % kWave == 0)
+        __shared__ int wdone[NT / kWave];
+        if (threadIdx.x % kWave == 0) {
             wsum[threadIdx.x / kWave] = rho2;
+            wdone[threadIdx.x / kWave] = done;
+        }
         __syncthreads();
         rho2 = 0.0;
-        for (int w = 0; w < NT / kWave; ++w)
+        for (int w = 0; w < NT / kWave; ++w) {
             rho2 += wsum[w];
+            done |= wdone[w];
+        }
     }
+    if (done)
+        return 1;
     const StopResult r = stop_decide(st, rho2, st->iter == 0);
     if (record && threadIdx.x == 0)
         stop_record(st, r, a.dbg_rho, a.hist, a.hist_cap);

@@ -74,3 +74,32 @@ def test_stops(hip, dims):
     with hip.Solver(op, 8, 20, pr.lmin, pr.lmax, max_outer=0) as sv:
         x, st = sv.solve(t64(b), None, 1e-8, raise_on_error=False)
         assert st.outer_iters == 0 and st.status == 5 and st.rel_res == 1.0
+
+
+# blocks of one wave, of four, bricks of sixteen; the last of each also without the
+# test in the launch
+STARTS = [("csr", (9, 8, 7)), ("csr", (32, 32, 32)), ("csr", (40, 40, 41)), ("27", (40, 40, 41)), ("7", (9, 8, 7)),
+          ("7", (40, 40, 41)), ("csr", (51, 52, 53)), ("7", (51, 52, 53))]
+
+
+@pytest.mark.parametrize("op,dims", STARTS, ids=lambda v: str(v).replace(" ", ""))
+def test_starts(hip, op, dims):
+    """A start from the solution (integers on a constant operator: the residual
+    is exactly zero) stops at once and stays as it is; from any other guess the
+    first iterate is the oracle's from there (1e-10)."""
+    pr = (gen.small_poisson27 if op == "27" else gen.small_poisson3d)(*dims, seed=5, s=8, nu=20)
+    A, b = oracle_rhs(pr)
+    r = gen.rng(12)
+    whole = np.rint(50 * gen.uniform(r, pr.n))
+    guess = gen.uniform(r, pr.n)
+    o = oracle.step(A, b, guess, 8, 20, pr.lmin, pr.lmax)
+    with hip.Solver(make_operator(hip, pr, "csr" if op == "csr" else "stencil"), 8, 20, pr.lmin, pr.lmax,
+                    max_outer=1) as sv:
+        for _ in range(3):  # a stop in the first launch, then a solve that goes on
+            x, st = sv.solve(t64(oracle.spmv(A, whole)), t64(whole), 1e-8)
+            assert (st.outer_iters, st.status, st.rel_res, st.res0) == (0, 0, 0.0, 0.0)
+            assert np.array_equal(x.cpu().numpy(), whole)
+            x, st = sv.solve(t64(b), t64(guess), 1e-14, raise_on_error=False)
+            assert (st.outer_iters, st.status) == (1, 5)
+            assert abs(st.res0 - o["rnorm"]) <= 1e-12 * o["rnorm"]
+            assert rel(x.cpu().numpy(), o["x"]) <= 1e-10
