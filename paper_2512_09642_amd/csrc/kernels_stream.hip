@@ -6,6 +6,7 @@
 #include "basis_brick.h"
 #include "launch.h"
 #include "march.h"
+#include "march_rule.h"
 #include "opsel.h"
 #include "stop.h"
 
@@ -544,12 +545,6 @@ constexpr int64_t kMarchResidual = 5 * (int64_t(1) << 16);
 // per point, 7-point FP64: 20 x 20 x 1500 14.6 / 9.2, 32 x 32 x 600 14.4 / 9.6, 300
 // x 8 x 300 14.6 / 9.3; 27-point equal; and above the line 300 x 300 x 8 8.7).
 constexpr double kMarchResidualFill = 1.0 / 3.0;
-// One basis step, by the bytes of a vector: 27-point FP64 64^3 / 96^3 / 224^3
-// 6.9 / 17.4 / 162 us against 8.6 / 12.4 / 52, FP32 96^3 / 128^3 8.0 / 16.9
-// against 8.6 / 11.2; 7-point FP64 with products 128^3 / 160^3 / 224^3 15.2 /
-// 25.9 / 67 against 15.9 / 23.1 / 47.5, FP32 the same at 160^3 and 224^3.
-constexpr int64_t kMarchStep27 = int64_t(4) << 20, kMarchStep7 = int64_t(24) << 20;
-
 // Grids that leave more than 9 of 11 lanes of their 64 x 32 tiles idle, or of
 // one plane: there the marched kernels give way to a thread per point (the
 // 7-point pairs to bricks).  us, marched against not, FP64: 16 x 16 x 4096
@@ -571,9 +566,13 @@ bool march_fits(const OpDev &op, int elem)
            f2_window_bytes(op.g, plan_march(op.g, op.kind == kOpPoisson27, elem).kz, elem) <= kF2MaxWindow;
 }
 
-bool march_step(const OpDev &op, int elem)
+// One basis step (march_rule.h).
+bool march_step(const IterArgs &a)
 {
-    return op.n * elem >= (op.kind == kOpPoisson27 ? kMarchStep27 : kMarchStep7) && march_fits(op, elem);
+    const Grid3 &g = a.op.g;
+    const int elem = a.fp32 ? 4 : 8;
+    return march_fits(a.op, elem) &&
+           march_step_pays(g.nx, g.ny, g.nz, a.op.kind == kOpPoisson27, elem, a.gram_mom, a.AP != nullptr);
 }
 
 template <typename TP, bool BOX>
@@ -743,7 +742,7 @@ hipError_t basis_csr(const IterArgs &a, int j, int step, hipStream_t st)
 template <typename T>
 hipError_t basis_t(const IterArgs &a, int j, int step, hipStream_t st)
 {
-    if (step != 2 && march_step(a.op, sizeof(T)))
+    if (step != 2 && march_step(a))
         return a.op.kind == kOpPoisson27 ? basis_march<T, true>(a, j, step, st) : basis_march<T, false>(a, j, step, st);
     switch (a.op.kind) {
     case kOpPoisson:
@@ -1258,7 +1257,7 @@ int basis_kernel_count(const IterArgs &a, int *pairs)
 bool small_chain(const IterArgs &a)
 {
     return a.gram_mom && a.op.n <= kSmallMax &&
-           (basis_pairs_apply(a) ? bricks_apply(a) && a.s % 2 == 0 : !march_step(a.op, 8));
+           (basis_pairs_apply(a) ? bricks_apply(a) && a.s % 2 == 0 : !march_step(a));
 }
 
 hipError_t launch_basis_all(const IterArgs &a, hipStream_t st)
@@ -1298,7 +1297,7 @@ void mom_layout(const IterArgs &a, int32_t *cnt, int64_t *stride)
             put(j, 2, nbl);
     }
     const int elem = a.fp32 ? 4 : 8;
-    const int64_t single = march_step(a.op, elem)
+    const int64_t single = march_step(a)
                                ? plan_march(a.op.g, a.op.kind == kOpPoisson27, elem).nbl
                                : plan_points(a.op.n, point_threads(a.op.n)).nbl;
     for (; j < m; ++j)

@@ -19,11 +19,13 @@
 #pragma once
 
 #include "basis_f2.h"
+#include "march_rule.h"
 
 namespace sstep {
 
 // Blocks that run at a time: the kernels below stay within 64 registers.
 constexpr int kMarchCus = 2 * kF2Cus;
+static_assert(kMarchLanes == kF2Lanes && kMarchRows == kF2Ext, "the rule counts the lanes of these tiles");
 
 // Planes per range by the same cost as plan_f2 (one plane below and one above
 // the range; the 27-point sums start one step earlier).
