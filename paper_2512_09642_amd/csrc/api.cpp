@@ -20,6 +20,7 @@
 #include <unistd.h>
 
 #include "launch.h"
+#include "replay.h"
 #include "sstep.h"
 #include "tune_cache.h"
 
@@ -722,15 +723,12 @@ sstep_status run_solve(sstep_ctx *ctx, const double *b, double *x, double tol, s
         ++launched;
         return e;
     };
-    HIPCHK(ctx, enqueue());
-    // One replay stays queued behind the one being waited for, so that the
-    // device does not wait for the host, unless the one in flight is expected
-    // to be the last: a replay after the stop still starts every kernel.  The
-    // expectation extrapolates the last two residuals read back.
+    // whether the replay in flight is expected to be the last, by extrapolating
+    // the last two residuals read back
     bool last = false;
     double relres = 1.0;
     for (;;) {
-        if (launched < max_replays && (!last || checked == launched))
+        while (queue_replay(launched, checked, max_replays, last))
             HIPCHK(ctx, enqueue());
         HIPCHK(ctx, hipEventSynchronize(ctx->ev_poll[checked % 2]));
         const DevState &h = ctx->st_host[checked % 2];
@@ -1898,9 +1896,8 @@ sstep_status sstep_solve_batched(sstep_ctx *ctx, const double *const *b, double 
         ++launched;
         return e;
     };
-    HIPCHK(ctx, enqueue());
     for (;;) {
-        if (launched < max_replays)
+        while (queue_replay(launched, checked, max_replays, false))
             HIPCHK(ctx, enqueue());
         HIPCHK(ctx, hipEventSynchronize(ctx->ev_poll[checked % 2]));
         const int32_t ndone = ctx->poll_host[4 * (checked % 2)];
