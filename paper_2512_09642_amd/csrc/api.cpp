@@ -1417,7 +1417,9 @@ static hipError_t enqueue_batched_iteration(const BatchArgs &a, hipStream_t s)
 // as they run) for each tile size and persistent-grid factor; keeps the
 // fastest pair, cached like the single-system Gram schedule.  The residual
 // runs on zeroed scratch right-hand sides and iterates, freed before
-// returning; without device memory for them the default schedule stays.
+// returning; without device memory for them the default schedule stays.  The
+// moments kind has none of these launches: it keeps the default schedule, which
+// the cache holds as not measured (0 us).
 static sstep_status tune_batched(sstep_ctx *ctx)
 {
     Batched &B = *ctx->batch;
@@ -1428,7 +1430,7 @@ static sstep_status tune_batched(sstep_ctx *ctx)
         h = (h ^ uint64_t(v)) * 1099511628211ull;
     key << kTuneSchema << " gfx950 batched s=" << a.s << " prec=" << (a.fp32 ? "fp32" : "fp64") << " nrhs=" << a.nrhs
         << " nsys=" << a.nsys << " faces=" << a.faces << " rec=" << a.rec << " mom=" << a.mom << " f2=" << a.f2
-        << " timed=iteration sizes=" << std::hex << h;
+        << " timed=iteration.2 sizes=" << std::hex << h;  // .2: without the update, which no schedule sets
     const std::string path = tune_cache_path();
     std::map<std::string, GramSchedule> cache;
     if (!path.empty()) {
@@ -1436,6 +1438,13 @@ static sstep_status tune_batched(sstep_ctx *ctx)
         auto f = cache.find(key.str());
         if (f != cache.end() && batched_entry_ok(f->second, kPad, kMinBatchChunk))
             return batched_tiles(ctx, f->second.slab, f->second.nbg, true);
+    }
+    if (a.mom) {
+        if (!path.empty()) {
+            cache[key.str()] = GramSchedule{B.grid_factor, B.gchunk, 0.0};
+            write_tune_cache(path, cache);
+        }
+        return SSTEP_OK;
     }
     struct Scratch {
         double *p = nullptr;
