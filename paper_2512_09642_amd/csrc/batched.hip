@@ -4,6 +4,7 @@
 // of pairs whose solve has stopped is skipped.  The Gram and FGS kernels of
 // the batched iteration live with the single-system ones (batched_impl.h).
 #include "band_f2.h"
+#include "grid_limits.h"
 #include "launch.h"
 
 namespace sstep {
@@ -422,7 +423,8 @@ __device__ __forceinline__ double basis_sum(const T *__restrict__ Pr, int64_t st
 }
 
 // x += P alpha for every pair whose solve continues: a block per kBlock points
-// of one pair, right-hand side after right-hand side.  HBM-bound: 20 systems of
+// of one pair, right-hand side after right-hand side, from block first on (a batch
+// of more than kBlocksPerLaunch takes several launches).  HBM-bound: 20 systems of
 // 32^3 to 96^3, 8 right-hand sides, s = 16, FP64: 1440 us with chunk tiles of
 // 2048 rows or more that walk the right-hand sides, 1370 (5.6 TB/s) with these;
 // 12 systems of 9^3 to 33^3, 3 right-hand sides, FP32+IR, whose 70 tiles left
@@ -431,12 +433,12 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void k_bupdate(const BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                     const PTile *__restrict__ tiles, uint32_t ntiles,
                                                     const DevState *__restrict__ pairs, int nrhs, int s,
-                                                    const T *__restrict__ P)
+                                                    const T *__restrict__ P, uint32_t first)
 {
     if (gl->ndone == gl->npairs)
         return;
-    const uint32_t r = blockIdx.x / ntiles;
-    const PTile tl = tiles[blockIdx.x - r * ntiles];
+    const uint32_t lb = first + blockIdx.x, r = lb / ntiles;
+    const PTile tl = tiles[lb - r * ntiles];
     const BSys &S = sys[tl.q];
     const DevState &ps = pairs[S.pair0 + r];
     const int64_t c = static_cast<int64_t>(tl.blk) * kBlock + threadIdx.x;
@@ -564,14 +566,17 @@ hipError_t launch_bbasis_pair(const BatchArgs &a, int j, hipStream_t st)
 hipError_t launch_bupdate(const BatchArgs &a, hipStream_t st)
 {
     const uint32_t npt = static_cast<uint32_t>(a.npt);
-    const dim3 grid(npt * static_cast<uint32_t>(a.nrhs));
-    if (a.fp32)
-        hipLaunchKernelGGL(k_bupdate<float>, grid, dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt, a.pairs, a.nrhs,
-                           a.s, static_cast<const float *>(a.P));
-    else
-        hipLaunchKernelGGL(k_bupdate<double>, grid, dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt, a.pairs, a.nrhs,
-                           a.s, static_cast<const double *>(a.P));
-    return hipGetLastError();
+    auto part = [&](uint64_t first, uint32_t blocks) -> hipError_t {
+        const uint32_t f = static_cast<uint32_t>(first);
+        if (a.fp32)
+            hipLaunchKernelGGL(k_bupdate<float>, dim3(blocks), dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt,
+                               a.pairs, a.nrhs, a.s, static_cast<const float *>(a.P), f);
+        else
+            hipLaunchKernelGGL(k_bupdate<double>, dim3(blocks), dim3(kBlock), 0, st, a.gl, a.sys, a.ptiles, npt,
+                               a.pairs, a.nrhs, a.s, static_cast<const double *>(a.P), f);
+        return hipGetLastError();
+    };
+    return in_launches(static_cast<uint64_t>(npt) * static_cast<uint64_t>(a.nrhs), hipSuccess, part);
 }
 
 }  // namespace sstep

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "basis_brick.h"
+#include "grid_limits.h"
 #include "launch.h"
 #include "march.h"
 #include "march_rule.h"
@@ -863,13 +864,19 @@ bool band_pairs_apply(const IterArgs &a)
 // 6.8 / 6.5, 80^3 6.8 / 7.6).  With face
 // coefficients not for an odd s, whose last column comes alone with another
 // count of partials; the constant operator takes two columns at any s, and
-// bricks in thin grids of any size (thin, above).
+// bricks in thin grids of any size (thin, above) whose bricks one launch holds
+// (2^22 of 1024 threads and more it does not: 1.1e9 unknowns in planes of 11 x 12,
+// 264 to a brick, march).
 constexpr int64_t kBrickMin = 2048, kBrickFaces = 1 << 18, kBrickConst = 3 << 17;
+constexpr int64_t kBrickSure = int64_t(1) << 21;  // no more bricks than unknowns: they fit one launch
 bool bricks_apply(const IterArgs &a)
 {
     if (a.op.kind == kOpFaces)
         return !a.fp32 && a.s % 2 == 0 && a.op.n >= kBrickMin && a.op.n <= kBrickFaces;
-    return a.op.kind == kOpPoisson && (a.op.n <= kBrickConst || thin(a.op.g));
+    if (a.op.kind != kOpPoisson)
+        return false;
+    return a.op.n <= kBrickConst ||
+           (thin(a.op.g) && (a.op.n < kBrickSure || launch_fits(plan_brick(a.op.g).per * kNumXcd, kBrickThreads)));
 }
 
 // The two-step kernels serve the Chebyshev basis of the constant operators and
