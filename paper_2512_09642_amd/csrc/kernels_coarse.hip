@@ -34,6 +34,7 @@
 // data (v, u, f, coefficients) are L2-resident.
 #include <algorithm>
 
+#include "coarse_steps.h"
 #include "launch.h"
 
 namespace sstep {
@@ -218,7 +219,7 @@ struct Formed {
     }
 };
 
-// One step: block row y takes sweep first + y, i.e. wavefront t0 - 8 y.
+// One step, or some of its sweeps (coarse_steps.h): block row y takes wavefront t0 - 8 y.
 template <class Form>
 __global__ __launch_bounds__(kBlock) void k_coarse_step(Form form, const int32_t *__restrict__ order,
                                                         const int32_t *__restrict__ wf, int t0)
@@ -267,18 +268,17 @@ hipError_t run_sweeps(const CoarseArgs &c, const Form &form, int nu, hipStream_t
     if (nu < 1)
         return hipGetLastError();
     const int64_t nc = static_cast<int64_t>(c.ncx) * c.ncy * c.ncz;
-    const int64_t steps = c.nwf + int64_t(8) * (nu - 1);
+    const int64_t steps = coarse_steps(c.nwf, nu);
     if (c.nwf <= kCoarseMaxFronts && nc <= kCoarseMaxUnknowns && nc * nu <= Form::kBlockActive * steps) {
         hipLaunchKernelGGL((k_coarse_sweeps<Form>), dim3(1), dim3(kCoarseThreads), 0, st, form, c.order, c.wf, c.nwf,
                            nu);
         return hipGetLastError();
     }
     const uint32_t bx = static_cast<uint32_t>((c.max_front * kHalf + kBlock - 1) / kBlock);
-    for (int64_t step = 0; step < steps; ++step) {
-        const int64_t l0 = step < c.nwf ? 0 : (step - c.nwf) / 8 + 1, l1 = std::min<int64_t>(step / 8, nu - 1);
-        hipLaunchKernelGGL((k_coarse_step<Form>), dim3(bx, static_cast<uint32_t>(l1 - l0 + 1)), dim3(kBlock), 0, st,
-                           form, c.order, c.wf, static_cast<int>(step - 8 * l0));
-    }
+    for (int64_t step = 0; step < steps; ++step)
+        step_launches(step, c.nwf, nu, [&](int t0, uint32_t rows) {
+            hipLaunchKernelGGL((k_coarse_step<Form>), dim3(bx, rows), dim3(kBlock), 0, st, form, c.order, c.wf, t0);
+        });
     return hipGetLastError();
 }
 
