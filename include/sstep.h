@@ -153,9 +153,10 @@ typedef struct {
                                Sec. 4 (a diagnostic: its Gram matrix is badly conditioned; the
                                bounds are then unused; not for batched contexts) */
     int32_t basis_steps;    /* 0 (default) = two basis steps per launch where the kernels allow it
-                               (constant 7-point operator, large 27-point grids, or batched
-                               stencil systems, when AP is not stored); 1 = one step per launch everywhere.  Both give the
-                               same basis bit for bit */
+                               (7-point operators, large 27-point grids and batched stencil
+                               systems, when AP is not stored; sstep_basis_launches tells);
+                               1 = one step per launch everywhere.  Both give the same basis bit
+                               for bit */
     void *stream;           /* hipStream_t the caller's data is ordered on (NULL = default) */
 } sstep_options;
 
@@ -298,8 +299,7 @@ int32_t sstep_gram_mode(const sstep_ctx *ctx);
  * unknowns and even s, and for batched stencil systems
  * with the recurrence Gram kind, one launch forms two consecutive columns
  * (p_{j+1} and p_{j+2} from p_{j-1} and p_j, exactly as two single steps
- * would; a single face-coefficient system's up to the rounding of the
- * operator), and *pairs (if pairs
+ * would), and *pairs (if pairs
  * is not NULL) receives how many launches do so; an odd m ends with a single
  * step.  Otherwise every launch forms one column and *pairs is 0.  A batched
  * context takes two steps per launch only when every system's grid row fits

@@ -9,19 +9,6 @@
 
 namespace sstep {
 
-// (A p)_c of the face operator from the differences of p_c to its neighbours.
-// The fused multiply-adds are written out: the single and the two-step basis
-// give the same bits whatever else surrounds the expression.
-template <typename T>
-__device__ __forceinline__ T face_sum(T fw, T dw, T fe, T de, T fs, T ds, T fn, T dn, T fb, T db, T ft, T dt)
-{
-    T y = __builtin_elementwise_fma(fw, dw, fe * de);
-    y = __builtin_elementwise_fma(fs, ds, y);
-    y = __builtin_elementwise_fma(fn, dn, y);
-    y = __builtin_elementwise_fma(fb, db, y);
-    return __builtin_elementwise_fma(ft, dt, y);
-}
-
 // Two neighbouring points of a lane, loaded and stored together: an 8-byte
 // access per lane takes the L1 as long as a 16-byte one.
 template <typename T>

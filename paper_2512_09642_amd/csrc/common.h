@@ -281,6 +281,20 @@ struct OpPoisson27 {
     }
 };
 
+// (A p)_c of the face operator from the differences of p_c to its neighbours.
+// The fused multiply-adds are written out: every kernel gives the same bits,
+// whatever else surrounds the expression, the single basis step those of the
+// two-step kernels among them.
+template <typename T>
+__device__ __forceinline__ T face_sum(T fw, T dw, T fe, T de, T fs, T ds, T fn, T dn, T fb, T db, T ft, T dt)
+{
+    T y = __builtin_elementwise_fma(fw, dw, fe * de);
+    y = __builtin_elementwise_fma(fs, ds, y);
+    y = __builtin_elementwise_fma(fn, dn, y);
+    y = __builtin_elementwise_fma(fb, db, y);
+    return __builtin_elementwise_fma(ft, dt, y);
+}
+
 // Variable-coefficient 7-point operator from face coefficients (boundary
 // faces included): (A p)_c = sum_f k_f (p_c - p_q), p_q = 0 outside.
 template <typename T>
@@ -314,7 +328,7 @@ struct OpFaces7 {
         const T n = j + 1 < static_cast<uint32_t>(g.ny) ? p[c + g.nx] : T(0);
         const T b = k > 0 ? p[c - g.nxy] : T(0);
         const T t = k + 1 < static_cast<uint32_t>(g.nz) ? p[c + g.nxy] : T(0);
-        y = fw * (pc - w) + fe * (pc - e) + fs * (pc - s) + fn * (pc - n) + fb * (pc - b) + ft * (pc - t);
+        y = face_sum(fw, pc - w, fe, pc - e, fs, pc - s, fn, pc - n, fb, pc - b, ft, pc - t);
         const T d = ((((fw + fe) + fs) + fn) + fb) + ft;
         dinv = precond ? T(1) / d : T(1);
         wt = precond ? d : T(1);
