@@ -17,7 +17,9 @@
 // kernels, with one partial sum per block: the product and alpha, then w and
 // beta.  No launch of its own sums the partials or divides by beta: every
 // block of the next pass sums them in the same order (at most 1024, 8 KB from
-// the L2), and the vectors stay w, their divisors applied where they are read.
+// the L2), and the vectors stay w, divided where they are read, entry by entry: a
+// factor common to the vector, the reciprocal of its norm, would carry one
+// rounding error into every entry.
 // 10 steps on a 128^3 faces operator, s = 16: 571 -> 447 us per call; the
 // product 19.7 us and w 16.0 us at 5.1 and 5.3 TB/s out of the last-level
 // cache (twice the blocks: 20.1 and 19.0), the Ritz values 43 -> 13.6 us.
@@ -137,7 +139,6 @@ __global__ __launch_bounds__(kBlock) void k_lz_apply(LzState *__restrict__ ls, c
     }
     if (stop)
         return;
-    const double inv = 1.0 / scale;
     const int64_t beg = static_cast<int64_t>(lb) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
     double acc = 0.0;
@@ -145,11 +146,11 @@ __global__ __launch_bounds__(kBlock) void k_lz_apply(LzState *__restrict__ ls, c
     for (int64_t c = beg + threadIdx.x; c < end; c += kBlock) {
         double pc, yy, dinv;
         op.apply(w, c, pc, yy, dinv);
-        yy *= inv;
+        yy /= scale;
         y[c] = yy;
-        acc += pc * inv * yy;
+        acc += pc * yy;
     }
-    block_partial(acc, pout + lb);
+    block_partial(acc / scale, pout + lb);
 }
 
 // w_{j+1} = M^{-1} y - alpha_j z_j - beta_j z_{j-1} (in place of y) and
@@ -170,22 +171,21 @@ __global__ __launch_bounds__(kBlock) void k_lz_orth(LzState *__restrict__ ls, Di
         ls->amax = fmax(ls->amax, fabs(alpha));
     }
     const double sj = j > 0 ? ab[steps + j - 1] : ls->scale;  // z_j = w_j / sj
-    const double ca = alpha / sj;
-    const double cb = j > 1 ? sj / ab[steps + j - 2] : j == 1 ? sj / ls->scale : 0.0;
+    const double sp = j > 1 ? ab[steps + j - 2] : ls->scale;  // and z_{j-1} = w_{j-1} / sp, beta_j = sj
     const int64_t beg = static_cast<int64_t>(lb) * chunk;
     const int64_t end = beg + chunk < n ? beg + chunk : n;
     double acc = 0.0;
     auto point = [&](int64_t c, double zp) {
         double d, di;
         dg.at(c, d, di);
-        const double v = di * y[c] - ca * w[c] - zp;
+        const double v = di * y[c] - alpha * (w[c] / sj) - sj * zp;
         y[c] = v;
         acc += d * v * v;
     };
     if (j > 0)
 #pragma unroll 4
         for (int64_t c = beg + threadIdx.x; c < end; c += kBlock)
-            point(c, cb * wprev[c]);
+            point(c, wprev[c] / sp);
     else
 #pragma unroll 4
         for (int64_t c = beg + threadIdx.x; c < end; c += kBlock)

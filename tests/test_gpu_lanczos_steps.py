@@ -38,3 +38,20 @@ def test_lanczos_steps(hip, dims, form, steps, scale):
     al, be = np.asarray(got["alpha"][:m]), np.asarray(got["beta"][:m - 1])
     ev = np.linalg.eigvalsh(np.diag(al) + np.diag(be, 1) + np.diag(be, -1))
     assert np.max(np.abs(np.asarray(got["ritz"][:m]) - ev)) <= 64 * np.finfo(float).eps * np.abs(ev).max()
+
+
+@pytest.mark.parametrize("op", ["7", "27", "csr"])
+def test_a_multiple_of_a_unit_vector(hip, op):
+    """From a whole multiple of a unit vector, without Jacobi, on a constant
+    operator: every entry is a whole number or its quotient by the norm, which is
+    a whole number again, so that alpha_0 is the diagonal entry and beta_1 the root
+    of the number of neighbours, to the bit."""
+    mk = gen.small_poisson27 if op == "27" else gen.small_poisson3d
+    pr = mk(12, 11, 10, seed=3, s=4, nu=5)
+    e = np.zeros(pr.n)
+    e[5 + 12 * (5 + 11 * 5)] = 1.0
+    with hip.Solver(make_operator(hip, pr, "csr" if op == "csr" else "stencil"), 4, 5, 0.0, 60.0, precond=False) as sv:
+        for a in (1.0, 49.0, 98.0, 103.0, 107.0, 161.0, 3e9):
+            r = sv.lanczos(torch.as_tensor(a * e, device="cuda:0"), 2)
+            k = 26.0 if op == "27" else 6.0
+            assert (r["alpha"][0], r["beta"][0]) == (k, np.sqrt(k)), a
