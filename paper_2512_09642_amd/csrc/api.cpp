@@ -139,7 +139,7 @@ sstep_status dalloc(sstep_ctx *ctx, T **p, size_t count)
 int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Copies count elements over dst: device arrays on the library's stream, which
-// has been made to wait for the caller's (order_after_user), host arrays
+// has been made to wait for the caller's (order_after_operator), host arrays
 // before returning.
 template <typename T>
 sstep_status overwrite_device(sstep_ctx *ctx, T *dst, const T *src, size_t count, int ptr_space)
@@ -164,6 +164,19 @@ sstep_status order_after_user(sstep_ctx *ctx)
 {
     HIPCHK(ctx, hipEventRecord(ctx->ev_in, ctx->user));
     HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    return SSTEP_OK;
+}
+
+// The same before it reads operator arrays in device memory.  Their copies used to
+// go through the default stream, so what that stream has been given is waited for
+// too, whichever stream the caller named.
+sstep_status order_after_operator(sstep_ctx *ctx)
+{
+    OKCHK(order_after_user(ctx));
+    if (ctx->user) {
+        HIPCHK(ctx, hipEventRecord(ctx->ev_in, nullptr));
+        HIPCHK(ctx, hipStreamWaitEvent(ctx->stream, ctx->ev_in, 0));
+    }
     return SSTEP_OK;
 }
 
@@ -897,7 +910,7 @@ static sstep_status setup_impl(sstep_ctx *ctx, const sstep_operator *A, int32_t 
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
     if (A->ptr_space)
-        OKCHK(order_after_user(ctx));
+        OKCHK(order_after_operator(ctx));
     {
         void *p = nullptr;
         HIPCHK(ctx, hipHostMalloc(&p, 2 * sizeof(DevState), hipHostMallocDefault));
@@ -1042,7 +1055,7 @@ sstep_status sstep_update_coefficients(sstep_ctx *ctx, const sstep_operator *A)
             return SSTEP_OK;  // no coefficients
     }
     if (A->ptr_space)
-        OKCHK(order_after_user(ctx));
+        OKCHK(order_after_operator(ctx));
     return load_coefficients(ctx, A, false);
 }
 
@@ -1574,7 +1587,7 @@ static sstep_status setup_batched_impl(sstep_ctx *ctx, int32_t nsys, const sstep
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t0));
     HIPCHK(ctx, hipEventCreate(&ctx->ev_t1));
     if (std::any_of(A, A + nsys, [](const sstep_operator &q) { return q.ptr_space != 0; }))
-        OKCHK(order_after_user(ctx));
+        OKCHK(order_after_operator(ctx));
     ctx->batch = new (std::nothrow) Batched();
     if (!ctx->batch)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");
@@ -1962,7 +1975,7 @@ static sstep_status coarse_setup_impl(sstep_ctx *ctx, const sstep_operator *Af, 
     ctx->user = static_cast<hipStream_t>(ctx->opt.stream);
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming));
     if (Af->ptr_space)
-        OKCHK(order_after_user(ctx));
+        OKCHK(order_after_operator(ctx));
     ctx->coarse = new (std::nothrow) CoarseArgs();
     if (!ctx->coarse)
         return fail(ctx, SSTEP_E_NOMEM, "out of host memory");

@@ -41,3 +41,30 @@ def test_faces_written_on_the_callers_stream(hip, side):
         assert torch.equal(sv.solve(b, None, 1e-12, raise_on_error=False)[0], want[0])
         sv.update_coefficients(hip.Operator.stencil(*pr.dims, *late(other, stream)))
         assert torch.equal(sv.solve(b, None, 1e-12, raise_on_error=False)[0], want[1])
+
+
+def test_faces_written_on_the_default_stream(hip):
+    """A solver on a stream of its own, the arrays from the default stream: the
+    set-up, the update, a batch and a coarse solver read them after that too."""
+    pr = gen.small_faces3d(31, 27, 25, seed=4, sigma=0.5)
+    b = torch.as_tensor(gen.uniform(gen.rng(2), pr.n), device=DEV)
+    side, default = torch.cuda.Stream(), torch.cuda.default_stream()
+    faces, other = [pr.kx, pr.ky, pr.kz], [2.0 * k + 1.0 for k in (pr.kx, pr.ky, pr.kz)]
+    nc = (15, 13, 12)
+    f = torch.as_tensor(gen.uniform(gen.rng(3), int(np.prod(nc))), device=DEV)
+    torch.cuda.synchronize()
+    got = []
+    for place in (lambda v: v, lambda v: late(v, default)):
+        with hip.Solver(hip.Operator.stencil(*pr.dims, *place(faces)), 8, 20, 0.0, 2.0, max_outer=3, stream=side) as sv:
+            x = [sv.solve(b, None, 1e-12, raise_on_error=False)[0]]
+            sv.update_coefficients(hip.Operator.stencil(*pr.dims, *place(other)))
+            x.append(sv.solve(b, None, 1e-12, raise_on_error=False)[0])
+        with hip.BatchedSolver([hip.Operator.stencil(*pr.dims, *place(faces))], 1, 8, 20, [0.0], [2.0], max_outer=3,
+                               stream=side) as bt:
+            x.append(bt.solve([b], None, 1e-12, raise_on_error=False)[0][0])
+        with hip.CoarseSolver(hip.Operator.stencil(*pr.dims, *place(faces)), stream=side) as cs:
+            x.append(cs.fgs(f, 3))
+        torch.cuda.synchronize()
+        got.append(x)
+    for a, c in zip(*got):
+        assert torch.equal(a, c)
