@@ -33,4 +33,24 @@ inline void step_launches(int64_t step, int64_t nwf, int64_t nu, F &&f)
         f(static_cast<int>(step - 8 * l), static_cast<uint32_t>(std::min(s.last - l + 1, kCoarseRows)));
 }
 
+// The steps one after the other, for a block that walks them itself.  The sweeps of
+// a step stand at the wavefronts oldest(), oldest() - 8, ..., newest(); steps without
+// any (between sweeps over fewer than 8 wavefronts) are left out.
+struct StepWalk {
+    int nwf, phase, active, left;  // phase: steps since the newest sweep began; left: sweeps not begun
+
+    constexpr StepWalk(int fronts, int nu) : nwf(fronts), phase(0), active(1), left(nu - 1) {}
+    constexpr bool more() const { return active > 0; }
+    constexpr int newest() const { return phase; }
+    constexpr int oldest() const { return phase + 8 * (active - 1); }
+    constexpr void next()
+    {
+        ++phase;
+        if (oldest() == nwf)
+            --active;
+        if (left > 0 && (phase == 8 || active == 0))
+            --left, ++active, phase = 0;
+    }
+};
+
 }  // namespace sstep

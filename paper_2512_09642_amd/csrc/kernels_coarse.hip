@@ -230,38 +230,46 @@ __global__ __launch_bounds__(kBlock) void k_coarse_step(Form form, const int32_t
         form.update(order[q], threadIdx.x % kHalf);
 }
 
-// All steps in one block, a barrier behind each.
-template <class Form>
+// All steps in one block (StepWalk), a barrier behind each that holds an unknown;
+// LDS: the tables are kept there (kCoarseMaxFronts, kCoarseMaxUnknowns).
+template <class Form, bool LDS>
 __global__ __launch_bounds__(kCoarseThreads) void k_coarse_sweeps(Form form, const int32_t *__restrict__ order,
                                                                   const int32_t *__restrict__ wf, int nwf, int nu)
 {
-    __shared__ int32_t start[kCoarseMaxFronts + 1], unknown[kCoarseMaxUnknowns];
-    for (int t = threadIdx.x; t <= nwf; t += kCoarseThreads)
-        start[t] = wf[t];
-    for (int q = threadIdx.x; q < wf[nwf]; q += kCoarseThreads)
-        unknown[q] = order[q];
-    __syncthreads();
-    const int half = threadIdx.x / kHalf, lane = threadIdx.x % kHalf;
-    for (int64_t step = 0; step < nwf + int64_t(8) * (nu - 1); ++step) {
-        const int64_t l0 = step < nwf ? 0 : (step - nwf) / 8 + 1, l1 = step / 8 < nu - 1 ? step / 8 : nu - 1;
-        int skip = half;  // unknowns of this step before the half wave's next one
-        for (int64_t l = l0; l <= l1; ++l) {
-            const int t = static_cast<int>(step - 8 * l), n = start[t + 1] - start[t];
-            for (; skip < n; skip += kCoarseThreads / kHalf)
-                form.update(unknown[start[t] + skip], lane);
-            skip -= n;
-        }
+    __shared__ int32_t start[LDS ? kCoarseMaxFronts + 1 : 1], unknown[LDS ? kCoarseMaxUnknowns : 1];
+    if constexpr (LDS) {
+        for (int t = threadIdx.x; t <= nwf; t += kCoarseThreads)
+            start[t] = wf[t];
+        for (int q = threadIdx.x; q < wf[nwf]; q += kCoarseThreads)
+            unknown[q] = order[q];
         __syncthreads();
+    }
+    const int half = threadIdx.x / kHalf, lane = threadIdx.x % kHalf;
+    for (StepWalk w(nwf, nu); w.more(); w.next()) {
+        int skip = half, total = 0;  // skip: unknowns of this step before the half wave's next one
+        for (int t = w.oldest(); t >= w.newest(); t -= 8) {
+            const int first = LDS ? start[t] : wf[t], n = (LDS ? start[t + 1] : wf[t + 1]) - first;
+            for (; skip < n; skip += kCoarseThreads / kHalf)
+                form.update(LDS ? unknown[first + skip] : order[first + skip], lane);
+            skip -= n;
+            total += n;
+        }
+        if (total > 0)  // the same in every thread
+            __syncthreads();
     }
 }
 
 // One block while it has few unknowns per step (kBlockActive of the form, on
 // average): a launch costs some 2 us whatever it holds, a pass of the block
 // grows with the unknowns its 32 half waves take in turn.  nu = 20, one block /
-// launches / the sweeps one after another in one block, us: streamed 5^3 471 /
-// 581 / 863, 7^3 770 / 666 / 1636, 17^3 8400 / 1200 / 16137; formed 7^3 380 /
+// launches / the sweeps one after another in one block, us: streamed 5^3 456 /
+// 581 / 863, 7^3 770 / 666 / 1636, 17^3 8400 / 1200 / 16137; formed 7^3 341 /
 // 492 / 942, 9^3 624 / 533 / 1551, 17^3 3300 / 790 / 6966; 31^3 streamed 1.95
-// against 95 ms.
+// against 95 ms.  Hierarchies whose tables do not fit the LDS are long ones, of
+// many steps with hardly any unknowns; the block then reads the tables for each
+// sweep of a step, so it takes few of them: streamed 1 x 1 x 3000 1 / 5 / 60
+// sweeps 4.6 / 10.2 / 86 ms against 40 / 40 / 42 in launches.
+constexpr int kBlockLongSweeps = 8;
 template <class Form>
 hipError_t run_sweeps(const CoarseArgs &c, const Form &form, int nu, hipStream_t st)
 {
@@ -269,9 +277,14 @@ hipError_t run_sweeps(const CoarseArgs &c, const Form &form, int nu, hipStream_t
         return hipGetLastError();
     const int64_t nc = static_cast<int64_t>(c.ncx) * c.ncy * c.ncz;
     const int64_t steps = coarse_steps(c.nwf, nu);
-    if (c.nwf <= kCoarseMaxFronts && nc <= kCoarseMaxUnknowns && nc * nu <= Form::kBlockActive * steps) {
-        hipLaunchKernelGGL((k_coarse_sweeps<Form>), dim3(1), dim3(kCoarseThreads), 0, st, form, c.order, c.wf, c.nwf,
-                           nu);
+    const bool fits = c.nwf <= kCoarseMaxFronts && nc <= kCoarseMaxUnknowns;
+    if (nc * nu <= Form::kBlockActive * steps && (fits || nu <= kBlockLongSweeps)) {
+        if (fits)
+            hipLaunchKernelGGL((k_coarse_sweeps<Form, true>), dim3(1), dim3(kCoarseThreads), 0, st, form, c.order,
+                               c.wf, c.nwf, nu);
+        else
+            hipLaunchKernelGGL((k_coarse_sweeps<Form, false>), dim3(1), dim3(kCoarseThreads), 0, st, form, c.order,
+                               c.wf, c.nwf, nu);
         return hipGetLastError();
     }
     const uint32_t bx = static_cast<uint32_t>((c.max_front * kHalf + kBlock - 1) / kBlock);

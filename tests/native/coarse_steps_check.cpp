@@ -1,6 +1,7 @@
 // The launches of coarse_steps.h for "nwf nu" given as arguments: every sweep takes
 // every wavefront once, at step t + 8 l, in launches of at most kCoarseRows rows;
-// prints the steps, launches and the most rows of one.
+// prints the steps, launches and the most rows of one.  The walk of one block
+// (StepWalk) takes the same steps.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -39,6 +40,24 @@ int main(int argc, char **argv)
                 return 5;
     if (most > 65535)
         return 6;
+    if (every == 1) {  // the same walked by one block
+        std::vector<int64_t> walked(size_t(nwf), 0);
+        int64_t ended = 0, held = 0;
+        for (sstep::StepWalk w{static_cast<int>(nwf), static_cast<int>(nu)}; w.more(); w.next()) {
+            ++held;
+            int64_t l = ended;
+            for (int t = w.oldest(); t >= w.newest(); t -= 8, ++l) {
+                if (t < 0 || t >= nwf || walked[size_t(t)]++ != l)
+                    return 7;
+                ended += t == nwf - 1;
+            }
+        }
+        for (int64_t v : walked)
+            if (v != nu)
+                return 8;
+        if (held != (nwf < 8 ? nwf * nu : steps))
+            return 9;
+    }
     std::printf("%ld %ld %ld\n", long(steps), long(launches), long(most));
     return 0;
 }

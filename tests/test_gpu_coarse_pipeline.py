@@ -29,3 +29,15 @@ def test_overlapped_sweeps_equal_sequential(hip, nc, nu, formed):
         again = cs.fgs(f, nu)
     assert rel(first.cpu().numpy(), want) <= 1e-10
     assert torch.equal(first, again)
+
+
+# long thin hierarchies walked by one block whose tables do not fit the LDS: more
+# than 1023 wavefronts, more than 4096 unknowns, both; and the same line again
+LONG = [((1, 1, 300), 1), ((1, 1, 300), 8), ((1, 1, 300), 9), ((1030, 1, 1), 4), ((2, 1, 700), 3), ((5000, 1, 1), 2), ((17, 17, 17), 1),
+        ((3, 40, 40), 1), ((1, 256, 1), 30)]
+
+
+@pytest.mark.parametrize("nc,nu", LONG)
+@pytest.mark.parametrize("formed", [False, True])
+def test_long_hierarchies(hip, nc, nu, formed):
+    test_overlapped_sweeps_equal_sequential(hip, nc, nu, formed)
