@@ -274,14 +274,24 @@ sstep_status setup_ell(sstep_ctx *ctx)
 {
     OpDev &op = ctx->it.op;
     const int64_t nslice = (op.n + kEllSlice - 1) / kEllSlice;
-    int32_t *count = nullptr;  // widths, then offsets
-    OKCHK(dalloc(ctx, &count, 2 * size_t(nslice)));
-    HIPCHK(ctx, launch_ell_plan(op, nslice, count, count + nslice, ctx->stream));
-    std::vector<int32_t> h(2 * size_t(nslice));
-    HIPCHK(ctx, hipMemcpyAsync(h.data(), count, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    std::vector<int32_t> h(3 * size_t(nslice));  // widths, offsets, spans
+    {
+        struct Counts {
+            int32_t *p = nullptr;
+            ~Counts()
+            {
+                if (p)
+                    (void)hipFree(p);
+            }
+        } c;
+        HIPCHK(ctx, hipMalloc(reinterpret_cast<void **>(&c.p), h.size() * sizeof(int32_t)));
+        HIPCHK(ctx, launch_ell_plan(op, nslice, c.p, c.p + nslice, c.p + 2 * nslice, ctx->stream));
+        HIPCHK(ctx, hipMemcpyAsync(h.data(), c.p, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+        HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+    }
     std::vector<EllSlice> slice(size_t(nslice), EllSlice{});
     int64_t nval = 0, ncol = 0, noff = 0;
+    double span = 0.0;
     for (int64_t q = 0; q < nslice; ++q) {
         EllSlice &S = slice[size_t(q)];
         S.diag = h[size_t(nslice + q)] > 0;
@@ -289,10 +299,12 @@ sstep_status setup_ell(sstep_ctx *ctx)
         S.val = nval;
         S.pat = S.diag ? noff : ncol;
         nval += int64_t(S.w) * kEllSlice;
-        if (S.diag)
+        if (S.diag) {
             noff += round_up(S.w, kEllGroup);
-        else
+        } else {
             ncol += int64_t(S.w) * kEllSlice;
+            span += double(S.w) * kEllSlice * h[size_t(2 * nslice + q)];
+        }
     }
     EllSlice *dslice = nullptr;
     int32_t *col = nullptr, *dofs = nullptr;
@@ -307,7 +319,8 @@ sstep_status setup_ell(sstep_ctx *ctx)
                                ctx->stream));
     op.ell_slice = dslice;
     op.ell_nslice = nslice;
-    op.ell_bytes = nval * int64_t(sizeof(double));
+    op.ell_values = nval;
+    op.ell_span = nval > 0 ? int64_t(span / double(nval)) : 0;
     op.ell_col = col;
     op.ell_val = val;
     op.ell_dofs = dofs;

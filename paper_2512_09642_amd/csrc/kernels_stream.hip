@@ -1032,7 +1032,7 @@ __device__ __forceinline__ int ell_merge(const int32_t *__restrict__ ci, int32_t
 
 __global__ __launch_bounds__(kBlock) void k_ell_plan(const int32_t *__restrict__ rp, const int32_t *__restrict__ ci,
                                                     int64_t n, int64_t nslice, int32_t *__restrict__ width,
-                                                    int32_t *__restrict__ offsets)
+                                                    int32_t *__restrict__ offsets, int32_t *__restrict__ span)
 {
     const int64_t r = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     const int64_t q = r / kEllSlice;
@@ -1042,9 +1042,12 @@ __global__ __launch_bounds__(kBlock) void k_ell_plan(const int32_t *__restrict__
     const int32_t w = -wave_min(-(k1 - k0));
     const int limit = static_cast<int>(int64_t(w) * 10 / 7);
     const int nd = ell_merge(ci, static_cast<int32_t>(r), k0, k1, limit, [](int, int32_t, bool) {});
+    // columns ascend within a row
+    const int32_t first = wave_min(k0 < k1 ? ci[k0] : 0x7fffffff), last = -wave_min(k0 < k1 ? -ci[k1 - 1] : 0);
     if (threadIdx.x % kWave == 0) {
         width[q] = w;
         offsets[q] = nd <= limit ? nd : 0;
+        span[q] = w > 0 ? last - first + 1 : 0;
     }
 }
 
@@ -1147,10 +1150,11 @@ __global__ __launch_bounds__(kBlock) void k_check_csr_cols(const int32_t *__rest
 
 }  // namespace
 
-hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, hipStream_t st)
+hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, int32_t *span,
+                           hipStream_t st)
 {
     hipLaunchKernelGGL(k_ell_plan, dim3(blocks_for(nslice * kEllSlice)), dim3(kBlock), 0, st, op.rp, op.ci, op.n,
-                       nslice, width, offsets);
+                       nslice, width, offsets, span);
     return hipGetLastError();
 }
 

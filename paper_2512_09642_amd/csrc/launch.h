@@ -50,7 +50,7 @@ struct OpDev {
     const int32_t *ell_dofs = nullptr;    // offsets and row masks of the others
     const uint64_t *ell_dmask = nullptr;
     int64_t ell_nslice = 0;
-    int64_t ell_bytes = 0;                // bytes of the values in FP64
+    int64_t ell_values = 0, ell_span = 0;  // entries, and how far their columns reach (ell_rule.h)
 };
 
 // Everything one outer iteration needs; all pointers are device memory.
@@ -265,10 +265,12 @@ int residual_march_blocks(const OpDev &op);
 int residual_threads(int64_t n);
 hipError_t launch_p0scale(const IterArgs &a, hipStream_t st);
 hipError_t launch_basis(const IterArgs &a, int j, hipStream_t st);
-// Sliced copy of a CSR operator (OpEll): per slice the longest row and the
-// offsets (0: too many, the slice is listed); the pattern; the values in FP64
-// or FP32 (from the CSR arrays rp, ci, val of the same precision).
-hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, hipStream_t st);
+// Sliced copy of a CSR operator (OpEll): per slice the longest row, the
+// offsets (0: too many, the slice is listed) and the rows from its first column to
+// its last; the pattern; the values in FP64 or FP32 (from the CSR arrays rp, ci,
+// val of the same precision).
+hipError_t launch_ell_plan(const OpDev &op, int64_t nslice, int32_t *width, int32_t *offsets, int32_t *span,
+                           hipStream_t st);
 hipError_t launch_ell_fill_pattern(const OpDev &op, int32_t *col, int32_t *dofs, uint64_t *dmask, hipStream_t st);
 hipError_t launch_ell_fill_val(const OpDev &op, const double *val, double *ev, hipStream_t st);
 hipError_t launch_ell_fill_val(const OpDev &op, const float *val, float *ev, hipStream_t st);

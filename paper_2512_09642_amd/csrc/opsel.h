@@ -2,6 +2,7 @@
 // an operator, in either precision.
 #pragma once
 
+#include "ell_rule.h"
 #include "launch.h"
 
 namespace sstep {
@@ -43,11 +44,6 @@ struct Ops<float> {
     }
 };
 
-// Matrix values of at most this many bytes go through the caches, which hold
-// them between products: basis step of a 7-point matrix, FP64, cached against
-// non-temporal: 101^3 15.2 / 17.5 us, 128^3 (134 MB with padding) 28.4 / 35.7,
-// 160^3 (257 MB) 65.3 / 65.4, 192^3 126 / 109.
-constexpr int64_t kEllKeepBytes = int64_t(192) << 20;
-inline bool ell_keep(const OpDev &op, int elem) { return op.ell_bytes / 8 * elem <= kEllKeepBytes; }
+inline bool ell_keep(const OpDev &op, int elem) { return ell_keep_pays(op.ell_values, op.ell_span, elem); }
 
 }  // namespace sstep
