@@ -1,8 +1,11 @@
 // Batched outer iteration over many stencil systems and right-hand sides:
 // residual + basis start, basis step, update and the FP32 scaling pre-pass.
-// Each kernel is persistent: a fixed grid walks a table of tiles, and the work
-// of pairs whose solve has stopped is skipped.  The Gram and FGS kernels of
-// the batched iteration live with the single-system ones (batched_impl.h).
+// The residual over chunk tiles, the single basis step and the Gram reduction are
+// persistent, a fixed grid walking a table of tiles; the two-step basis and its
+// residual take a block per band and right-hand side, the update one per 256 points
+// of a pair.  The work of pairs whose solve has stopped is skipped.  The Gram and
+// FGS kernels of the batched iteration live with the single-system ones
+// (batched_impl.h).
 #include "band_f2.h"
 #include "grid_limits.h"
 #include "launch.h"

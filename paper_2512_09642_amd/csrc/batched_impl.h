@@ -213,8 +213,8 @@ __device__ __forceinline__ void bfgs_map_sweep(BGlob *__restrict__ gl, DevState 
         pair_stopped(gl, Q);
 }
 
-// Recurrence Gram kind: the pair's sums of H and c', then H mapped onto G_raw = P^T A P with the system's theta, sigma (as k_fgs_rec
-// does) and the FGS wave.
+// Recurrence Gram kind: the pair's sums of H and c', then H mapped onto G_raw =
+// P^T A P with the system's theta, sigma (as k_fgs_rec does) and the FGS wave.
 template <int S>
 __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_rec(BGlob *__restrict__ gl, const BSys *__restrict__ sys,
                                                            DevState *__restrict__ pairs, int nrhs,
@@ -232,7 +232,6 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_rec(BGlob *__restrict__ g
     const int r = p % nrhs;
     __shared__ double h[E1];
     __shared__ double sg[T0 + S];
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const double *gp = gpart + Q.gofs + static_cast<int64_t>(r) * E1 * Q.nch;
     block_sums(gp, Q.nch, E1, h);
     __syncthreads();
@@ -271,7 +270,6 @@ __global__ __launch_bounds__(kBFgsThreads) void k_bfgs_mom(BGlob *__restrict__ g
     __shared__ double mu[NS];
     __shared__ double h[E1];
     __shared__ double sg[T0 + S];
-    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     // slots 0 .. NS - 1: the products (slot NS: ||r||^2, k_bres_f2)
     const double *mp = mpart + Q.mofs + static_cast<int64_t>(r) * bmom_slots(S) * Q.nf2q;
     block_sums(mp, Q.nf2q, NS, m);

@@ -154,15 +154,7 @@ __global__ __launch_bounds__(kBlock) void k_coarse_zero(double *__restrict__ a, 
 constexpr int kHalf = kWave / 2;  // lanes per unknown
 
 // Sum over the 32 lanes of a half wave, in a fixed order; every lane gets it.
-__device__ __forceinline__ double half_sum(double v)
-{
-    v = add_rows<16>(v);
-    v += dpp<kDppRor8>(v);
-    v += dpp<kDppRor4>(v);
-    v += dpp<kDppXor2>(v);
-    v += dpp<kDppXor1>(v);
-    return v;
-}
+__device__ __forceinline__ double half_sum(double v) { return row_sum(add_rows<16>(v)); }
 
 // One update of unknown j by half a wave, streamed: lane l < 27 owns fine
 // point (2I + l%3, 2J + (l/3)%3, 2K + l/9) of p_j's support.

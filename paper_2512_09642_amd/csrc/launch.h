@@ -275,7 +275,8 @@ hipError_t launch_ell_fill_pattern(const OpDev &op, int32_t *col, int32_t *dofs,
 hipError_t launch_ell_fill_val(const OpDev &op, const double *val, double *ev, hipStream_t st);
 hipError_t launch_ell_fill_val(const OpDev &op, const float *val, float *ev, hipStream_t st);
 // The whole basis p_1 .. p_m of one outer iteration: two steps per launch
-// for the constant 7-point operator without stored AP, else one per launch.
+// without stored AP for the constant 7-point operator, large 27-point grids and
+// most sizes of face-coefficient systems (basis_kernel_count), else one per launch.
 hipError_t launch_basis_all(const IterArgs &a, hipStream_t st);
 // Moments kind: the basis launch that starts at column j writes its products
 // from slot 0 (j = 0: <p_0,Mp_0>, <p_1,Mp_0>, <p_1,Mp_1>, ...) or from slot
@@ -289,7 +290,8 @@ hipError_t launch_mom_sums(const IterArgs &a, hipStream_t st);
 // them form two columns.
 int basis_kernel_count(const IterArgs &a, int *pairs);
 // Whether an outer iteration is so short that its launches are what it costs
-// (moments kind, a thread per point in every basis launch).
+// (moments kind; bricks or a thread per point in every basis launch, all with the
+// same count of partials).
 bool small_chain(const IterArgs &a);
 // AP[:, j] = A p_j alone (into a.AP, which must be set).
 hipError_t launch_product(const IterArgs &a, int j, hipStream_t st);

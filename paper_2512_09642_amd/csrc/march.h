@@ -12,8 +12,8 @@
 // sum formed once per point instead of 27 loads per point.  Values are formed
 // with the operations of OpPoisson7 / OpPoisson27 (common.h), in their order.
 //
-// What bounds it: HBM at large grids (27-point residual at 230^3 305 -> 53 us,
-// 5.5 TB/s algorithmic; 7-point at 224^3 62.5 -> 50 us, stopping test
+// What bounds it: HBM at large grids (27-point residual at 230^3 in a solve 371 -> 58
+// us, 5.1 TB/s algorithmic; 7-point at 224^3 62.5 -> 50 us, stopping test
 // included), the chain of planes at small ones, where a thread per point is
 // kept.
 #pragma once
