@@ -58,6 +58,7 @@ inline BrickPlan plan_brick(const Grid3 &g)
                 const BrickPlan p = brick_plan(x, y, z);
                 if (!best.nbl || p.nbl < best.nbl)
                     best = p;
+                break;  // a shorter one of these takes no fewer blocks (planned for each launch of a solve without a graph)
             }
     return best;
 }
